@@ -265,9 +265,10 @@ __device__ __forceinline__ double rsq(double x)
 // finite at |S| = 0; unguarded, that case runs through infinities and NaNs
 // that the final select discards, with the same result and two selects
 // fewer (taken where the kernel's register allocation stays spill-free).
+// Without SELECT the caller sees to |S| = 0.
 // The squared moduli are written as explicit FMAs so that every kernel
 // variant rounds them alike.
-template <bool RELAX, typename R, bool GUARD = true>
+template <bool RELAX, typename R, bool GUARD = true, bool SELECT = true>
 __device__ __forceinline__ typename cx<R>::T local_update(typename cx<R>::T g0, typename cx<R>::T s, R omega)
 {
     using C = typename cx<R>::T;
@@ -287,8 +288,10 @@ __device__ __forceinline__ typename cx<R>::T local_update(typename cx<R>::T g0, 
         g.x = vx * rv;
         g.y = vy * rv;
     }
-    g.x = ok ? g.x : g0.x;
-    g.y = ok ? g.y : g0.y;
+    if (SELECT) {
+        g.x = ok ? g.x : g0.x;
+        g.y = ok ? g.y : g0.y;
+    }
     return g;
 }
 

@@ -142,7 +142,10 @@ hipError_t gc_launch_lanczos(int d, int block, int seg, int form, const GcJobDev
                              unsigned long long *next, int grid, size_t lds_bytes, hipStream_t s);
 
 // Table and bookkeeping kernels.
-hipError_t gc_launch_reset(const GcJobDev *jobs_host, int n_jobs, hipStream_t s);
+// reset: table, records and counters; with start_states also every start's
+// state row (what the team relaxation kernels begin from).
+hipError_t gc_launch_reset(const GcJobDev *jobs_host, int n_jobs, bool start_states, hipStream_t s);
+hipError_t gc_launch_start_states(const GcJobDev &job_host, hipStream_t s);
 hipError_t gc_launch_finalize(const GcJobDev *jobs_host, int n_jobs, hipStream_t s);   // representatives + compaction
 hipError_t gc_launch_orbit_random(double *phi, int64_t n_links, uint64_t seed, uint64_t orbit_index, hipStream_t s);
 

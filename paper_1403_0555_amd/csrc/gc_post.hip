@@ -477,10 +477,40 @@ __global__ __launch_bounds__(B) void post_kernel(const GcJobDev *__restrict__ jo
     }
 }
 
-__global__ void reset_kernel(GcJobDev J)
+// Start states, natural site order: the caller's angles or Philox's, four
+// sites (one Philox block) per thread.
+__device__ __forceinline__ void start_states(const GcJobDev &J, uint64_t gid, uint64_t stride)
+{
+    const uint32_t V = (uint32_t)J.orb.V, nb = (V + 3) / 4;
+    glb_ptr<dbl2> rows = as_global(reinterpret_cast<dbl2 *>(J.states));
+    for (uint64_t t = gid; t < J.n_starts * nb; t += stride) {
+        const uint64_t local = t / nb;
+        const uint32_t b = (uint32_t)(t - local * nb);
+        uint64_t w[4];
+        // the caller's start angles, else Philox (the block is skipped then)
+        if (!J.theta_init) start_block(J.start_seed, J.first_start + local, J.orb.orbit_index, b, w);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t i = 4 * b + q;
+            if (i < V) {
+                double sn, cs;
+                sincos(J.theta_init ? J.theta_init[local * V + i] : angle_of(w[q]), &sn, &cs);
+                rows[local * V + i] = dbl2{cs, sn};
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void start_states_kernel(GcJobDev J)
+{
+    start_states(J, (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, (uint64_t)gridDim.x * blockDim.x);
+}
+
+template <bool STATES> __global__ __launch_bounds__(256) void reset_kernel(GcJobDev J)
 {
     const uint64_t gid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    if constexpr (STATES) start_states(J, gid, stride);
     for (uint64_t t = gid; t <= J.table_mask; t += stride) {
         GcEntry e;
         e.key_hi = 0;
@@ -832,16 +862,28 @@ hipError_t gc_launch_lanczos(int d, int block, int seg, int form, const GcJobDev
     }
 }
 
-hipError_t gc_launch_reset(const GcJobDev *jobs_host, int n_jobs, hipStream_t s)
+hipError_t gc_launch_reset(const GcJobDev *jobs_host, int n_jobs, bool start_states, hipStream_t s)
 {
     for (int j = 0; j < n_jobs; ++j) {
         const GcJobDev &J = jobs_host[j];
-        const uint64_t work = J.table_mask + 1 > J.n_starts ? J.table_mask + 1 : J.n_starts;
-        hipLaunchKernelGGL(reset_kernel, dim3(grid_for(work)), dim3(256), 0, s, J);
+        uint64_t work = J.table_mask + 1 > J.n_starts ? J.table_mask + 1 : J.n_starts;
+        if (start_states) {
+            work = std::max<uint64_t>(work, J.n_starts * (uint64_t)((J.orb.V + 3) / 4));
+            hipLaunchKernelGGL(reset_kernel<true>, dim3(grid_for(work)), dim3(256), 0, s, J);
+        } else {
+            hipLaunchKernelGGL(reset_kernel<false>, dim3(grid_for(work)), dim3(256), 0, s, J);
+        }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+hipError_t gc_launch_start_states(const GcJobDev &J, hipStream_t s)
+{
+    const uint64_t work = J.n_starts * (uint64_t)((J.orb.V + 3) / 4);
+    hipLaunchKernelGGL(start_states_kernel, dim3(grid_for(work)), dim3(256), 0, s, J);
+    return hipGetLastError();
 }
 
 hipError_t gc_launch_finalize(const GcJobDev *jobs_host, int n_jobs, hipStream_t s)

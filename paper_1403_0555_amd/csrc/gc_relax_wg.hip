@@ -1,4 +1,6 @@
-// Relaxation kernel for any lattice (any number of checkerboard colours):
+// Relaxation kernel for any lattice (any number of checkerboard colours), used
+// where no team kernel is instantiated (gc_team.h: odd rings, more than seven
+// colours, the largest odd lattices):
 // one workgroup holds one random start in LDS, in natural site order, and
 // pulls the next start from a device-wide counter when its start is done.
 //

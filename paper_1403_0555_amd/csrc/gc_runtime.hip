@@ -10,6 +10,7 @@
 // overlap on the device.
 #include "../../include/gribov.h"
 #include "gc_internal.h"
+#include "gc_team.h"
 #include "gc_wave.h"
 
 #include <algorithm>
@@ -215,20 +216,23 @@ struct HostCopies {
     void clear() { n = 0; }
 };
 
-// Relax launch groups: orbits with odd extents use the workgroup-per-start
-// kernel; orbits with even extents the wavefront-per-start kernel, one launch
-// per dimension, layout and slot count (the kernel is specialised on them).
+// Relax launch groups: the team kernels, one launch per dimension, colours and
+// wavefronts; where none is instantiated, even extents take the
+// wavefront-per-start kernel (few sites) or the workgroup-per-start kernel
+// (many), odd extents the generic workgroup kernel.
 struct Group {
     bool wave = false;
     int d = 0;
     std::vector<int> jobs;           // indices into Job::orbits
-    int block = 64, grid = 1, ns = 1, coef_lds = 0, creg = 0, wps = 0;
-    int rm = 0;                      // relax mode of the exchange-region kernel (ns > 2)
-    int full = 0;                    // GC_RM_FULL_SLOTS for the double-precision kernel, or 0
+    int block = 64, grid = 1, coef_lds = 0, creg = 0, wps = 0;
     size_t lds = 0;
-    // mixed precision above two slots per lane: the single-precision phase
-    // in its own kernel, before the double-precision one
-    int split = 0, grid32 = 1;
+    // team kernels: shape (cls 0: another kernel), colours, relax mode and the
+    // most starts a workgroup takes at once; in mixed precision the
+    // single-precision phase is a launch of its own before the
+    // double-precision one
+    GcTeamShape team{0, 0};
+    int K = 0, rm = 0, mmax = 1;
+    int split = 0, grid32 = 1, mmax32 = 1;
     size_t lds32 = 0;
     size_t o_jobs = 0, o_worbs = 0, o_next = 0, o_prefix = 0, o_bounce = 0;
     size_t o_jobs1 = 0;              // first-pass descriptors of a batch-synchronous launch
@@ -236,7 +240,7 @@ struct Group {
 };
 
 // Kernel variant word of a wavefront-per-start group (gc_launch_wave).
-int wave_variant(const Group &g) { return g.coef_lds | (g.creg << 1) | ((g.rm | g.full) << 3); }
+int wave_variant(const Group &g) { return g.coef_lds | (g.creg << 1); }
 
 // Orbits of one relax group sharing one post-kernel shape (workgroup size by
 // V), so that an orbit's per-start arithmetic is the same alone and in a
@@ -523,10 +527,6 @@ gc_status build_orbit(gc_ctx *ctx, Orbit *o)
         std::vector<uint16_t> nb((size_t)2 * half * 8, 0);
         std::vector<double2> c64((size_t)2 * 2 * d * half);
         std::vector<float2> c32((size_t)2 * 2 * d * half);
-        const bool scaled = 16 * (size_t)half <= 0xFFFF;
-        std::vector<uint16_t> nbo(scaled ? (size_t)2 * half * 8 : 0, 0), nbo32(scaled ? (size_t)2 * half * 8 : 0, 0);
-        std::vector<double2> l64((size_t)2 * d * half);
-        std::vector<float2> l32((size_t)2 * d * half);
         for (int c = 0; c < 2; ++c)
             for (int h = 0; h < half; ++h) {
                 const int i = site[(size_t)c * half + h];
@@ -534,15 +534,9 @@ gc_status build_orbit(gc_ctx *ctx, Orbit *o)
                     const int mu = k < d ? k : k - d;
                     const int nsite = k < d ? nbr[(size_t)mu * V + i] : nbr[(size_t)(d + mu) * V + i];
                     nb[((size_t)c * half + h) * 8 + k] = (uint16_t)(nsite >> 1);
-                    if (scaled) {
-                        nbo[((size_t)c * half + h) * 8 + k] = (uint16_t)(16 * (nsite >> 1));
-                        nbo32[((size_t)c * half + h) * 8 + k] = (uint16_t)(8 * (nsite >> 1));
-                    }
                     double2 u;
                     if (k < d) {
                         u = U64[(size_t)mu * V + i];
-                        l64[((size_t)c * d + mu) * half + h] = u;
-                        l32[((size_t)c * d + mu) * half + h] = make_float2((float)u.x, (float)u.y);
                     } else {
                         u = U64[(size_t)mu * V + nsite];
                         u.y = -u.y;
@@ -554,19 +548,12 @@ gc_status build_orbit(gc_ctx *ctx, Orbit *o)
         size_t woff = 0;
         auto wplace = [&](size_t bytes) { size_t at = woff; woff = align_up(woff + bytes, 256); return at; };
         const size_t w_loc = wplace(loc.size() * 2), w_nb = wplace(nb.size() * 2), w_c64 = wplace(c64.size() * 16),
-                     w_c32 = wplace(c32.size() * 8),
-                     w_nbo = wplace(nbo.size() * 2), w_nbo32 = wplace(nbo32.size() * 2), w_l64 = wplace(l64.size() * 16), w_l32 = wplace(l32.size() * 8);
+                     w_c32 = wplace(c32.size() * 8);
         std::vector<unsigned char> wh(woff, 0);
         memcpy(&wh[w_loc], loc.data(), loc.size() * 2);
         memcpy(&wh[w_nb], nb.data(), nb.size() * 2);
         memcpy(&wh[w_c64], c64.data(), c64.size() * 16);
         memcpy(&wh[w_c32], c32.data(), c32.size() * 8);
-        if (scaled) {
-            memcpy(&wh[w_nbo], nbo.data(), nbo.size() * 2);
-            memcpy(&wh[w_nbo32], nbo32.data(), nbo32.size() * 2);
-        }
-        memcpy(&wh[w_l64], l64.data(), l64.size() * 16);
-        memcpy(&wh[w_l32], l32.data(), l32.size() * 8);
         void *wdevmem = nullptr;
         GC_HIP(ctx->pool.get(woff, &wdevmem, &got));
         o->wave_tables = wdevmem;
@@ -578,10 +565,6 @@ gc_status build_orbit(gc_ctx *ctx, Orbit *o)
         o->wdev.nb = (const uint4 *)(wb + w_nb);
         o->wdev.coef64 = (const double2 *)(wb + w_c64);
         o->wdev.coef32 = (const float2 *)(wb + w_c32);
-        o->wdev.nbo = scaled ? (const uint4 *)(wb + w_nbo) : nullptr;
-        o->wdev.nbo32 = scaled ? (const uint4 *)(wb + w_nbo32) : nullptr;
-        o->wdev.link64 = (const double2 *)(wb + w_l64);
-        o->wdev.link32 = (const float2 *)(wb + w_l32);
     }
     return GC_OK;
 }
@@ -625,18 +608,6 @@ void give_event(gc_ctx *ctx, hipEvent_t &e, bool timing)
     e = nullptr;
 }
 
-// The instantiated slot count of the one-wavefront kernel for ns slots per
-// lane (orbits of one bucket share a kernel).
-int ns_bucket(int d, int ns)
-{
-    static const int b1[] = {1, 4, 12, 16}, b2[] = {1, 2, 4, 12, 16}, b3[] = {2, 4, 8, 16}, b4[] = {1, 2, 4, 11, 16};
-    const int *b = d == 1 ? b1 : d == 2 ? b2 : d == 3 ? b3 : b4;
-    const int nb = d == 1 ? 4 : d == 2 ? 5 : d == 3 ? 4 : 5;
-    for (int k = 0; k < nb; ++k)
-        if (ns <= b[k]) return b[k];
-    return 16;
-}
-
 // Layout of a job's device block and its launch groups.  Each orbit runs the
 // context's tuned kernel variant for its shape unless the job forces one
 // (autotune trials).  Orbits are grouped by relax kernel; each group is one
@@ -664,37 +635,48 @@ gc_status plan_job(gc_ctx *ctx, Job *job, JobLayout &L)
         L.o_states.push_back(place(sizeof(double2) * n * (uint64_t)o->V));
         L.o_sync.push_back(job->p.sync_batch ? place(sizeof(uint32_t) * n) : 0);
         L.o_theta.push_back(job->theta.empty() ? 0 : place(sizeof(double) * n * (uint64_t)o->V));
-        // two colours: one wavefront per start (GC_WAVES states per
-        // workgroup in LDS) up to 128 slots per colour, a workgroup of wps
-        // wavefronts per start above; other colourings take the generic
-        // workgroup kernel
+        // slots per lane if one wavefront held a start; GC_WPS = 1 forces the
+        // workgroup layout where it is instantiated (more than two)
         const int o_ns = (o->V / 2 + 63) / 64;
         int wps = (o->K == 2) ? gc_wps_for(o_ns) : -1;
-        if (wps > 0 && (size_t)(GC_WAVES + 1) * 16 * o->V <= ctx->lds_max) {
-            // both layouts fit: one wavefront per start (the exchange-region
-            // kernel measured several times faster than a workgroup per
-            // start, and it keeps one reduction order for a shape), unless
-            // the context forces the workgroup layout
-            if (ctx->wps_override <= 0) wps = 0;
+        // the team kernels where one is instantiated and its states fit
+        GcTeamShape team = gc_team_shape(o->d, o->K, o->V);
+        if (team.cls && ((ctx->wps_override > 0 && wps > 0) ||
+                         gc_team_lds_bytes(o->d, o->K, team, o->V, false) > ctx->lds_max))
+            team.cls = 0;
+        if (team.cls) {
+            Group *g = nullptr;
+            for (Group &x : L.groups)
+                if (x.team.cls == team.cls && x.d == o->d && x.K == o->K && x.team.waves == team.waves) g = &x;
+            if (!g) {
+                L.groups.push_back(Group{});
+                g = &L.groups.back();
+                g->team = team;
+                g->d = o->d;
+                g->K = o->K;
+            }
+            g->jobs.push_back(j);
+            g->total += n;
+            continue;
         }
+        // two colours: one wavefront per start up to 64 sites per colour, a
+        // workgroup of wps wavefronts per start above; other colourings take
+        // the generic workgroup kernel
         if (wps > 0 && 32 * (size_t)o->V > ctx->lds_max) wps = -1;
-        const bool wave = (o->K == 2) && wps >= 0 && (wps > 0 || (size_t)(GC_WAVES + 1) * 16 * o->V <= ctx->lds_max);
-        // groups by kernel: dimension, layout and instantiated slot count,
-        // or (generic) block size; an orbit's arithmetic does not depend on
-        // the other orbits of its group
+        const bool wave = (o->K == 2) && (wps > 0 || (wps == 0 && o_ns == 1));
+        // groups by kernel: dimension and layout, or (generic) block size; an
+        // orbit's arithmetic does not depend on the other orbits of its group
         const int gd = wave ? o->d : -block_for(o->V);
-        const int gw = wave ? std::max(wps, 0) : 0;
-        const int gb = (wave && gw == 0) ? ns_bucket(o->d, o_ns) : 0;
+        const int gw = wave ? wps : 0;
         Group *g = nullptr;
         for (Group &x : L.groups)
-            if (x.wave == wave && x.d == gd && x.wps == gw && x.ns == gb) g = &x;
+            if (!x.team.cls && x.wave == wave && x.d == gd && x.wps == gw) g = &x;
         if (!g) {
             L.groups.push_back(Group{});
             g = &L.groups.back();
             g->wave = wave;
             g->d = gd;
             g->wps = gw;
-            g->ns = gb;
         }
         g->jobs.push_back(j);
         g->total += n;
@@ -703,60 +685,52 @@ gc_status plan_job(gc_ctx *ctx, Job *job, JobLayout &L)
         int gV = 0;
         for (int j : g.jobs) gV = std::max(gV, job->orbits[j]->V);
         int per_cu = 0;
-        if (g.wave && g.wps > 0) {
+        if (g.team.cls) {
+            g.block = 64 * g.team.waves;
+            g.rm = (job->p.omega == 1.0 ? 1 : 0) | (job->p.stop_norm ? 2 : 0);
+            g.split = mixed ? 1 : 0;
+            // as many workgroups as fit; a launch of fewer starts than they
+            // hold at m each spreads them evenly
+            auto fit = [&](bool f32, size_t &lds, int &grid, int &mmax) -> hipError_t {
+                lds = gc_team_lds_bytes(g.d, g.K, g.team, gV, f32);
+                int pc = 0;
+                const hipError_t e = gc_team_occupancy(g.d, g.K, g.team, f32, lds, &pc);
+                if (e != hipSuccess) return e;
+                const uint64_t wgs = (uint64_t)std::max(pc, 1) * ctx->n_cu;
+                grid = (int)std::min<uint64_t>(wgs, std::max<uint64_t>(g.total, 1));
+                mmax = (int)std::min<uint64_t>(gc_team_class(g.d, g.K, g.team.cls).m, (g.total + grid - 1) / grid);
+                return hipSuccess;
+            };
+            hipError_t e = fit(false, g.lds, g.grid, g.mmax);
+            if (e == hipSuccess && g.split) e = fit(true, g.lds32, g.grid32, g.mmax32);
+            if (e != hipSuccess) return fail(ctx, e, "occupancy");
+            per_cu = 0;
+        } else if (g.wave && g.wps > 0) {
             g.block = 64 * g.wps;
             g.lds = 32 * (size_t)gV;   // neighbour table + one state
             hipError_t e = gc_wps_occupancy(g.d, g.wps, g.lds, &per_cu);
             if (e != hipSuccess) return fail(ctx, e, "occupancy");
         } else if (g.wave) {
-            g.ns = (gV / 2 + 63) / 64;
-            g.block = 64 * gc_wave_starts_per_wg(g.ns);
-            g.rm = g.ns > 2 ? gc_wave_relax_mode(job->p.omega, job->p.stop_norm) : 0;
-            // every orbit fills all slots of a lane but the last: the
-            // double-precision kernel tests only the last slot
-            if (g.ns > 2) {
-                bool full = true;
-                for (int j : g.jobs) full = full && (job->orbits[j]->V / 2 + 63) / 64 == ns_bucket(g.d, g.ns);
-                g.full = full ? GC_RM_FULL_SLOTS : 0;
-            }
+            g.block = 64 * GC_WAVES;
             size_t coef_bytes = 0;
             for (int j : g.jobs) {
                 const Orbit *o = job->orbits[j];
                 coef_bytes = std::max(coef_bytes, (size_t)2 * o->d * o->V * (mixed ? 24 : 16));
             }
-            // neighbour table + states (two-colour regions of 16V, or 8V
-            // exchange regions of the register-resident kernel) + links
-            // staged in LDS
-            const size_t states = g.ns > 2 ? gc_rr_lds_bytes(g.d, ns_bucket(g.d, g.ns), gV)
-                                           : (size_t)(GC_WAVES + 1) * 16 * gV;
-            // a staged coefficient table only where a lane has at most two
-            // slots; above, the links are read through buffer loads
-            g.coef_lds = (g.ns <= 2 && coef_bytes + states <= 64 * 1024) ? 1 : 0;
+            // neighbour table + states (two-colour regions of 16V)
+            const size_t states = (size_t)(GC_WAVES + 1) * 16 * gV;
+            g.coef_lds = coef_bytes + states <= 64 * 1024 ? 1 : 0;
             g.lds = states + (g.coef_lds ? coef_bytes : 0);
             if (g.lds > ctx->lds_max) return GC_EUNSUPPORTED;
-            // colour-0 coefficients in registers by default where a lane has
-            // at most two slots: the uneven 32-orbit batch runs 1.4-2.2 %
-            // faster so than with none, though 4^4 alone is faster with none
-            // (44.7 against 49.9 ms per step), which the autotuner finds;
-            // GC_WAVE_CREG overrides
-            g.creg = std::min(1, gc_wave_creg_max(g.d, g.ns));
-            const auto tc = ctx->tune_creg.find(creg_key(g.d, g.ns, mixed));
-            if (tc != ctx->tune_creg.end()) g.creg = std::min(tc->second, gc_wave_creg_max(g.d, g.ns));
-            if (ctx->creg_override >= 0) g.creg = std::min(ctx->creg_override, gc_wave_creg_max(g.d, g.ns));
-            if (job->force_creg >= 0) g.creg = std::min(job->force_creg, gc_wave_creg_max(g.d, g.ns));
-            hipError_t e = gc_wave_occupancy(g.d, g.ns, wave_variant(g), g.lds, &per_cu);
+            // colour-0 coefficients in registers by default; the autotuner and
+            // GC_WAVE_CREG override
+            g.creg = 1;
+            const auto tc = ctx->tune_creg.find(creg_key(g.d, 1, mixed));
+            if (tc != ctx->tune_creg.end()) g.creg = std::min(tc->second, GC_WAVE_CREG_MAX);
+            if (ctx->creg_override >= 0) g.creg = std::min(ctx->creg_override, GC_WAVE_CREG_MAX);
+            if (job->force_creg >= 0) g.creg = std::min(job->force_creg, GC_WAVE_CREG_MAX);
+            hipError_t e = gc_wave_occupancy(g.d, wave_variant(g), g.lds, &per_cu);
             if (e != hipSuccess) return fail(ctx, e, "occupancy");
-            if (g.ns > 2 && mixed) {
-                g.split = 1;
-                g.lds32 = gc_rr32_lds_bytes(g.d, ns_bucket(g.d, g.ns), gV);
-                if (g.lds32 > ctx->lds_max) return GC_EUNSUPPORTED;
-                int pc32 = 0;
-                e = gc_wave32_occupancy(g.d, g.ns, g.rm, g.lds32, &pc32);
-                if (e != hipSuccess) return fail(ctx, e, "occupancy");
-                pc32 = std::max(pc32, 1);
-                g.grid32 = (int)std::min<uint64_t>((uint64_t)pc32 * ctx->n_cu,
-                                                   std::max<uint64_t>((g.total + GC_WAVES_RR32 - 1) / GC_WAVES_RR32, 1));
-            }
         } else {
             g.block = block_for(gV);
             g.lds = gc_relax_wg_lds_bytes(gV);
@@ -764,19 +738,20 @@ gc_status plan_job(gc_ctx *ctx, Job *job, JobLayout &L)
             hipError_t e = gc_relax_wg_occupancy(g.block, g.lds, &per_cu);
             if (e != hipSuccess) return fail(ctx, e, "occupancy");
         }
-        per_cu = std::max(per_cu, 1);
-        const uint64_t per_wg = (g.wave && g.wps == 0) ? (uint64_t)gc_wave_starts_per_wg(g.ns) : 1;
-        uint64_t grid = (uint64_t)per_cu * (uint64_t)ctx->n_cu;
-        grid = std::min<uint64_t>(grid, std::max<uint64_t>((g.total + per_wg - 1) / per_wg, 1));
-        g.grid = (int)grid;
+        const uint64_t per_wg = (g.wave && g.wps == 0) ? (uint64_t)GC_WAVES : 1;
+        if (!g.team.cls) {
+            per_cu = std::max(per_cu, 1);
+            uint64_t grid = (uint64_t)per_cu * (uint64_t)ctx->n_cu;
+            grid = std::min<uint64_t>(grid, std::max<uint64_t>((g.total + per_wg - 1) / per_wg, 1));
+            g.grid = (int)grid;
+        }
         g.o_jobs = place(sizeof(GcJobDev) * g.jobs.size());
         g.o_jobs1 = job->p.sync_batch ? place(sizeof(GcJobDev) * g.jobs.size()) : 0;
         g.o_worbs = place(sizeof(GcWaveOrbit) * g.jobs.size());
         g.o_next = place(sizeof(unsigned long long) * g.jobs.size());
         g.o_prefix = place(sizeof(uint64_t) * (g.jobs.size() + 1));
-        // promotion scratch of the two-region kernels (the register-resident
-        // kernel promotes in registers)
-        g.o_bounce = (g.wave && (g.wps > 0 || g.ns <= 2)) ? place(sizeof(float2) * (size_t)gV * per_wg * g.grid) : 0;
+        // promotion scratch of the wavefront- and workgroup-per-start kernels
+        g.o_bounce = g.wave ? place(sizeof(float2) * (size_t)gV * per_wg * g.grid) : 0;
     }
     // key pass: one workgroup per start, one launch per workgroup shape
     // within each relax group's chain; filter pass: one workgroup per copy,
@@ -1020,7 +995,7 @@ hipError_t enqueue_chain(Job *job, unsigned char *base, int gi, hipStream_t qs, 
     const Group &g = L.groups[gi];
     hipError_t e = hipSuccess;
     for (int j : g.jobs) {
-        e = gc_launch_reset(&job->jobs[j], 1, qs);
+        e = gc_launch_reset(&job->jobs[j], 1, g.team.cls != 0, qs);
         if (e != hipSuccess) return e;
     }
     e = gc_launch_zero_u64((unsigned long long *)(base + g.o_next), (int)g.jobs.size(), qs);
@@ -1037,22 +1012,28 @@ hipError_t enqueue_chain(Job *job, unsigned char *base, int gi, hipStream_t qs, 
     }
     if (timed && (e = hipEventRecord(job->ev_k0, qs)) != hipSuccess) return e;
     auto relax = [&](size_t o_jobs) -> hipError_t {
+        if (g.team.cls) {
+            const GcJobDev *dj = (const GcJobDev *)(base + o_jobs);
+            unsigned long long *next = (unsigned long long *)(base + g.o_next);
+            if (g.split) {
+                // single precision, then double precision from the promoted
+                // states; omega may round to 1 in single precision only
+                const int rm32 = ((float)job->p.omega == 1.0f ? 1 : 0) | (g.rm & 2);
+                hipError_t e2 = gc_launch_team(g.d, g.K, g.team, true, rm32, dj, (int)g.jobs.size(), next, g.mmax32,
+                                               g.grid32, g.lds32, qs);
+                if (e2 == hipSuccess) e2 = gc_launch_zero_u64(next, (int)g.jobs.size(), qs);
+                if (e2 != hipSuccess) return e2;
+            }
+            return gc_launch_team(g.d, g.K, g.team, false, g.rm, dj, (int)g.jobs.size(), next, g.mmax, g.grid, g.lds,
+                                  qs);
+        }
         if (g.wave && g.wps > 0)
             return gc_launch_wps(g.d, g.wps, (const GcJobDev *)(base + o_jobs),
                                  (const GcWaveOrbit *)(base + g.o_worbs), (int)g.jobs.size(),
                                  (unsigned long long *)(base + g.o_next), (float2 *)(base + g.o_bounce), g.grid,
                                  g.lds, qs);
-        if (g.wave && g.split) {
-            // single precision, then double precision from the promoted states
-            hipError_t e2 = gc_launch_wave32(g.d, g.ns, (const GcJobDev *)(base + o_jobs),
-                                             (const GcWaveOrbit *)(base + g.o_worbs), (int)g.jobs.size(),
-                                             (unsigned long long *)(base + g.o_next), g.rm, g.grid32, g.lds32, qs);
-            if (e2 == hipSuccess)
-                e2 = gc_launch_zero_u64((unsigned long long *)(base + g.o_next), (int)g.jobs.size(), qs);
-            if (e2 != hipSuccess) return e2;
-        }
         if (g.wave)
-            return gc_launch_wave(g.d, g.ns, (const GcJobDev *)(base + o_jobs),
+            return gc_launch_wave(g.d, (const GcJobDev *)(base + o_jobs),
                                   (const GcWaveOrbit *)(base + g.o_worbs), (int)g.jobs.size(),
                                   (unsigned long long *)(base + g.o_next), wave_variant(g),
                                   (float2 *)(base + g.o_bounce), g.grid, g.lds, qs);
@@ -1064,8 +1045,10 @@ hipError_t enqueue_chain(Job *job, unsigned char *base, int gi, hipStream_t qs, 
         // batch-synchronous stop: a first pass finds every start's own
         // stopping sweep, the second runs each batch to its largest
         if ((e = relax(g.o_jobs1)) != hipSuccess) return e;
-        for (int j : g.jobs)
+        for (int j : g.jobs) {
             if ((e = gc_launch_sync(&job->jobs[j], 1, qs)) != hipSuccess) return e;
+            if (g.team.cls && (e = gc_launch_start_states(job->jobs[j], qs)) != hipSuccess) return e;
+        }
         e = gc_launch_zero_u64((unsigned long long *)(base + g.o_next), (int)g.jobs.size(), qs);
         if (e != hipSuccess) return e;
     }
@@ -2292,9 +2275,9 @@ gc_status gc_autotune(gc_ctx *ctx, gc_orbit orbit, uint64_t n_starts, const gc_s
         return s2;
     };
     gc_tune_result r{};
-    const bool wave = (K == 2) && (size_t)(GC_WAVES + 1) * 16 * V <= ctx->lds_max;
-    const int ns = (V / 2 + 63) / 64;
-    const int cmax = wave ? gc_wave_creg_max(d, ns) : 0;
+    // only the wavefront-per-start kernel has variants to choose from
+    const bool wave = K == 2 && V / 2 <= 64;
+    const int cmax = wave ? GC_WAVE_CREG_MAX : 0;
     double rm = 0, pm = 0;
     st = trial(-1, &rm, &pm);   // warm-up: code objects, pool
     if (st != GC_OK) return st;
@@ -2317,7 +2300,7 @@ gc_status gc_autotune(gc_ctx *ctx, gc_orbit orbit, uint64_t n_starts, const gc_s
     }
     {
         std::lock_guard<std::mutex> g(ctx->mu);
-        if (wave) ctx->tune_creg[creg_key(d, ns, mixed)] = best_c;
+        if (wave) ctx->tune_creg[creg_key(d, 1, mixed)] = best_c;
         save_tune_cache(ctx);
     }
     // the filter's shape depends on the lattice only: reported, not tuned

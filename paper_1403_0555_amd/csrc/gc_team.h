@@ -1,0 +1,64 @@
+// Team relaxation kernels (gc_team_kern.h): shapes and launch entry points.
+#pragma once
+
+#include "gc_internal.h"
+
+// An instantiation: spt sites of each colour per thread, m starts in step, at
+// most maxw wavefronts per workgroup, compiled for minw wavefronts per SIMD
+// (512 / minw registers), pf neighbours fetched ahead.
+struct GcTeamClass {
+    int spt, m, maxw, minw, pf;
+};
+
+// Classes by dimension and colours.  The links and neighbour offsets of a
+// thread's sites, 10 d K registers, set the register budget, the budget the
+// wavefronts per SIMD, and the LDS of 160 KiB the starts in step.  Measured,
+// 10^9 site updates per second at 100 sweeps of 10^5 starts (over-relaxed,
+// double precision), against the kernels these replaced (a wavefront, or
+// with odd extents a workgroup, per start): 6^4 290 against 257, 10^3 415
+// against 317, 8^3 404 against 296, 12^3 367 against 204, 32^2 491 against
+// 290, 4^4 312 against 175, 16^2 445 against 386, 9^3 253 against 78; and a
+// sweep of a single start: 6^4 1.5 against 5.9 us, 10^3 1.2 against 3.8, 12^3
+// 1.6 against 10.8, 9^3 2.0 against 6.0.  The clock falls from 2.2 to 1.9 GHz
+// as the vector units fill: the power limit takes part of what a better
+// overlap would give.
+constexpr GcTeamClass gc_team_class(int d, int K, int cls)
+{
+    if (K == 2) {
+        if (d <= 2)
+            return cls == 1 ? GcTeamClass{1, 3, 4, 4, 2 * d} : cls == 2 ? GcTeamClass{1, 3, 8, 4, 2 * d}
+                                                                        : GcTeamClass{1, 3, 16, 4, 2 * d};
+        if (d == 3)
+            return cls == 1 ? GcTeamClass{1, 3, 4, 3, 4} : cls == 2 ? GcTeamClass{1, 3, 8, 4, 1}
+                                                                    : GcTeamClass{1, 3, 16, 4, 1};
+        return cls == 1 ? GcTeamClass{1, 3, 4, 3, 0}
+                        : cls == 2 ? GcTeamClass{1, 7, 8, 2, 4}
+                                   : cls == 3 ? GcTeamClass{1, 3, 12, 3, 1} : GcTeamClass{2, 3, 8, 2, 1};
+    }
+    if (K == 3 && d == 2) return cls == 1 ? GcTeamClass{1, 3, 4, 4, 0} : GcTeamClass{1, 3, 8, 4, 0};
+    if (K == 3 && d == 3) return cls == 1 ? GcTeamClass{1, 3, 4, 3, 0} : GcTeamClass{1, 3, 8, 2, 0};
+    return GcTeamClass{1, 3, 8, 2, 0};
+}
+
+// Shape of the team kernel for a lattice: its class (0: none, the other relax
+// kernels take the lattice) and the wavefronts per workgroup.
+struct GcTeamShape {
+    int cls, waves;
+};
+GcTeamShape gc_team_shape(int d, int K, int V);
+
+// LDS: m states with a place per thread and colour, the norm's partial sums
+// (of the last colour apart with two colours), the positions of the V sites.
+constexpr size_t gc_team_lds_bytes(int d, int K, const GcTeamShape &s, int V, bool f32)
+{
+    const GcTeamClass c = gc_team_class(d, K, s.cls);
+    return (size_t)64 * s.waves * c.m * ((f32 ? 8 : 16) * K * c.spt + (K == 2 ? 16 : 8)) + 2 * (size_t)V;
+}
+
+// f32: the single-precision phase of a mixed launch (converged starts are
+// promoted into their state row for the double-precision launch that
+// follows); rm: bit 0 plain relaxation, bit 1 the max |div| norm; mmax: the
+// most starts a workgroup takes at once (1 .. m).
+hipError_t gc_team_occupancy(int d, int K, const GcTeamShape &s, bool f32, size_t lds, int *per_cu);
+hipError_t gc_launch_team(int d, int K, const GcTeamShape &s, bool f32, int rm, const GcJobDev *jobs, int n_jobs,
+                          unsigned long long *job_next, int mmax, int grid, size_t lds, hipStream_t st);

@@ -1,0 +1,58 @@
+"""Team relaxation kernels (one workgroup, several starts in step) against the
+oracle, start by start, at the edges of their shapes: half volumes of one site
+more than a wavefront holds, the first and last of each wavefront count's
+range, two sites per thread, three, five and seven colours, and launches with
+more starts than the workgroups hold, so that places are refilled."""
+import numpy as np
+import pytest
+
+import gribov_inputs as GI
+import paper_1403_0555_amd as gc
+from oracle import oracle as O
+
+from tests.test_gpu_parity import compare_starts, oracle_params, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    with gc.Context(0) as c:
+        yield c
+
+
+@pytest.mark.parametrize("extent", [
+    (132,), (2, 66), (16, 16), (2, 130), (2, 258), (32, 32), (2, 1024),      # 1D and 2D, 2 to 16 wavefronts
+    (2, 4, 18), (4, 6, 6), (8, 8, 8), (2, 2, 130), (2, 2, 258), (12, 12, 12), (8, 16, 16),
+    (2, 2, 2, 18), (4, 4, 4, 4), (2, 4, 8, 8), (2, 2, 2, 66), (4, 6, 6, 6), (2, 2, 2, 130), (6, 6, 6, 6),
+    (4, 6, 8, 8), (2, 4, 10, 20), (8, 8, 8, 4),                              # 4D, two sites per thread in the last
+    (3, 3), (9, 15), (3, 3, 3, 3), (3, 6, 9), (9, 9, 9), (3, 21, 21), (3, 3, 9, 9),
+    (5, 5), (5, 5, 5), (5, 5, 5, 5), (7, 7), (7, 7, 7),
+])
+@pytest.mark.parametrize("kw", [{"omega": 1.7}, {"omega": 1.0, "max_sweeps": 40, "stop_norm": "max_abs", "eps64": 1e-3},
+                                {"omega": 1.6, "check_every": 3}])
+def test_team_kernels_match_the_oracle(ctx, extent, kw):
+    n = 24 if GI.volume(extent) > 600 else 48
+    phi = GI.orbit_angles(extent, 3, 1)
+    p = gc.SolveParams(first_start=5, **{"max_sweeps": 150, **kw})
+    h, _, starts, _ = run_gpu(ctx, extent, phi, n, p, orbit_index=1)
+    rec, _, _ = O.solve(extent, phi, 5 + np.arange(n), oracle_params(p, 1))
+    compare_starts(extent, starts, rec)
+    ctx.gc_release(h)
+
+
+@pytest.mark.parametrize("extent,n", [((16, 16), 6000), ((2, 2, 2, 18), 6000), ((6, 6, 6), 6000), ((3, 3, 3), 6000)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_refilled_places_do_not_depend_on_the_launch(ctx, extent, n, precision):
+    """A start's record is the same in a launch of many starts (places are
+    refilled many times over) and in one of few."""
+    phi = GI.orbit_angles(extent, 4, 2)
+    h, _, many, prog = run_gpu(ctx, extent, phi, n, gc.SolveParams(omega=1.7, precision=precision), orbit_index=2)
+    assert prog["starts_done"] == n and np.all(many["status"] == 1)
+    few = n - 37
+    h2, _, last, _ = run_gpu(ctx, extent, phi, 37, gc.SolveParams(omega=1.7, precision=precision, first_start=few),
+                             orbit_index=2)
+    for f in ("status", "sweeps32", "sweeps64", "F", "D", "key_hi", "key_lo"):
+        assert np.array_equal(many[f][few:], last[f]), f
+    ctx.gc_release(h)
+    ctx.gc_release(h2)

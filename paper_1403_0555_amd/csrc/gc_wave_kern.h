@@ -67,6 +67,15 @@ __device__ __forceinline__ typename cx<R>::T staple(const typename cx<R>::T (&cf
     return s;
 }
 
+// The largest volume of a launch's jobs: the stride of the promotion scratch,
+// whose regions then stay apart while wavefronts work on different jobs.
+__device__ __forceinline__ int max_volume(const GcJobDev *jobs, int n_jobs)
+{
+    int v = 0;
+    for (int j = 0; j < n_jobs; ++j) v = max(v, jobs[j].orb.V);
+    return uniform(v);
+}
+
 // Synchronisation and reductions over the WPS wavefronts that share a start
 // (WPS = 1: one wavefront; otherwise the whole workgroup).  red holds at
 // least WPS doubles of LDS.
@@ -335,6 +344,7 @@ __global__ __launch_bounds__(64 * WAVES) void wave_kernel(const GcJobDev *__rest
     __shared__ int cur_job;
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
+    const int vmax = max_volume(jobs, n_jobs);
     int j0 = (int)(blockIdx.x % (unsigned)n_jobs);
     for (int round = 0; round < n_jobs; ++round) {
         if (threadIdx.x == 0) {
@@ -380,7 +390,7 @@ __global__ __launch_bounds__(64 * WAVES) void wave_kernel(const GcJobDev *__rest
         lds_ptr<dbl2> st64 = as_lds(reinterpret_cast<dbl2 *>(smem + off + (size_t)wave * 16 * V));
         lds_ptr<flt2> st32 = as_lds(reinterpret_cast<flt2 *>(smem + off + (size_t)wave * 16 * V));
         glb_ptr<flt2> bounce =
-            as_global(reinterpret_cast<flt2 *>(bounce_all) + ((uint64_t)blockIdx.x * WAVES + wave) * (uint64_t)V);
+            as_global(reinterpret_cast<flt2 *>(bounce_all) + ((uint64_t)blockIdx.x * WAVES + wave) * (uint64_t)vmax);
         for (;;) {
             unsigned long long s = 0;
             if (lane == 0) s = atomicAdd(&job_next[jn], 1ULL);
@@ -411,6 +421,7 @@ __global__ __launch_bounds__(64 * WPS) void wps_kernel(const GcJobDev *__restric
     __shared__ int cur_job;
     __shared__ unsigned long long claim;
     __shared__ double red[WPS];
+    const int vmax = max_volume(jobs, n_jobs);
     int j0 = (int)(blockIdx.x % (unsigned)n_jobs);
     for (int round = 0; round < n_jobs; ++round) {
         if (threadIdx.x == 0) {
@@ -437,7 +448,7 @@ __global__ __launch_bounds__(64 * WPS) void wps_kernel(const GcJobDev *__restric
         __syncthreads();
         lds_ptr<dbl2> st64 = as_lds(reinterpret_cast<dbl2 *>(smem + 16 * (size_t)V));
         lds_ptr<flt2> st32 = as_lds(reinterpret_cast<flt2 *>(smem + 16 * (size_t)V));
-        glb_ptr<flt2> bounce = as_global(reinterpret_cast<flt2 *>(bounce_all) + (uint64_t)blockIdx.x * (uint64_t)V);
+        glb_ptr<flt2> bounce = as_global(reinterpret_cast<flt2 *>(bounce_all) + (uint64_t)blockIdx.x * (uint64_t)vmax);
         const dbl2 *g64 = reinterpret_cast<const dbl2 *>(WO.coef64);
         const flt2 *g32 = reinterpret_cast<const flt2 *>(WO.coef32);
         lds_ptr<const u32x4> nbc = nbt;

@@ -115,3 +115,26 @@ def test_uneven_batch_matches_oracle():
                 assert np.array_equal(s2[f], starts[f], equal_nan=starts[f].dtype.kind == "f"), f
         for h in hs:
             ctx.gc_release(h)
+
+
+def test_mixed_batch_of_unequal_volumes_is_reproducible():
+    """The single-to-double promotion goes through per-wavefront scratch; the
+    regions of a launch's wavefronts stay apart while they work on orbits of
+    different volumes (both shapes run in one kernel launch)."""
+    shapes = [(4, 4), (10, 12)] * 6
+    with gc.Context(0) as ctx:
+        hs = [ctx.gc_orbit_load(e, GI.orbit_angles(e, 6, k), k) for k, e in enumerate(shapes)]
+        p = gc.SolveParams(omega=1.7, precision="mixed")
+        n = 1500
+        alone = []
+        for h in hs:
+            ctx.gc_launch(h, n, p)
+            assert ctx.gc_wait(h, 120_000) == gc.GC_OK
+            alone.append(ctx.gc_fetch_starts(h, n))
+        for _ in range(3):
+            ctx.gc_launch_batch(hs, [n] * len(hs), p)
+            for h, a in zip(hs, alone):
+                assert ctx.gc_wait(h, 120_000) == gc.GC_OK
+                s = ctx.gc_fetch_starts(h, n)
+                for f in ("status", "sweeps32", "sweeps64", "F", "D", "key_hi", "key_lo"):
+                    assert np.array_equal(s[f], a[f]), f

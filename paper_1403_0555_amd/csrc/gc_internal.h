@@ -8,6 +8,7 @@
 #define GC_MAXD 4
 #define GC_MAXPT 16        // sites per thread held in registers by the Lanczos step
 #define GC_LMAX 512        // Lanczos iteration cap (tridiagonal storage)
+#define GC_TRI_PAD 8       // rows past the tridiagonal's last in the line-segment filter
 
 // Per-start status codes (mirror GC_START_* of the public header).
 #define GC_ST_PENDING 0
@@ -135,7 +136,7 @@ hipError_t gc_launch_post(int block, int sp, int wreg, int keys, const GcJobDev 
 int gc_lanczos_shape(int d, const int *ext, int V, int *block, int *seg);
 int gc_lanczos_form(int N0, int seg, int V, int block);
 // LDS bytes: u and the weight arrays, seg x stride doubles each, then the
-// tridiagonal.
+// tridiagonal and its padding.
 size_t gc_lanczos_lds_bytes(int d, int N0, int seg, int V, int lmax, int block);
 hipError_t gc_lanczos_occupancy(int d, int block, int seg, int form, size_t lds_bytes, int *blocks_per_cu);
 hipError_t gc_launch_lanczos(int d, int block, int seg, int form, const GcJobDev *jobs, int n_jobs,

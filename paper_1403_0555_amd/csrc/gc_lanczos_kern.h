@@ -7,20 +7,214 @@
 
 namespace {
 
-// The Ritz value of a check, computed by the first wavefront alone (a
-// 65-section per round: a quarter of the vector work of the whole
-// workgroup's multisection for one more round at most) and handed to the
-// others through LDS.  The workgroup synchronises before (the tridiagonal is
-// complete in LDS) and after.
+// The Lanczos tridiagonal in LDS, row j as (alpha_j, beta_{j-1}^2), followed
+// by kTriPad rows past the last.
+typedef __attribute__((address_space(3))) const dbl2 lds_cdbl2;
+constexpr int kTriPad = GC_TRI_PAD;
+
+// p_k(x) = det(T_k - x) up to a positive smooth factor, as f 2^e, and whether
+// an eigenvalue lies below x: the Sturm sequence of sturm_count (gc_filter.h)
+// has a sign change.  Rows come four at a time, loaded one block ahead; rows
+// past the last stand for alpha = 64 > x, beta = 0 and keep every sign.  The
+// pair is rescaled after eight rows: |alpha - x| < 2^7 and beta^2 < 2^10
+// leave it in range.  A row takes three double-precision and two integer
+// instructions on the wavefront, 20 cycles (64 with the rows loaded where
+// they are used, signs counted and a rescaling every four rows).
+struct SturmValue {
+    double f;
+    int e;
+    bool below;
+};
+__device__ __forceinline__ SturmValue sturm_value(lds_cdbl2 *tri, int k, double x)
+{
+    double p0 = 0.0, p1 = 1.0;
+    uint32_t signs = 0;
+    int e = 0;
+    auto rows = [&](const dbl2 (&row)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const double p2 = fma(row[u].x - x, p1, -row[u].y * p0);
+            signs |= (uint32_t)(((uint64_t)__double_as_longlong(p2) ^ (uint64_t)__double_as_longlong(p1)) >> 32);
+            p0 = p1;
+            p1 = p2;
+        }
+    };
+    dbl2 ra[4], rb[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) ra[u] = tri[u];
+    for (int j = 0; j < k; j += 8) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) rb[u] = tri[j + 4 + u];
+        rows(ra);
+        const int jn = min(j + 8, k);   // the rows past the last where no block follows
+#pragma unroll
+        for (int u = 0; u < 4; ++u) ra[u] = tri[jn + u];
+        rows(rb);
+        int q;
+        (void)frexp(p1, &q);
+        p0 = ldexp(p0, -q);
+        p1 = ldexp(p1, -q);
+        e += q;
+    }
+    return {p1, e, (signs >> 31) != 0};
+}
+
+__device__ __forceinline__ double lane_value(double v, int l)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+// a / b to about 2^-45: the estimate refined once.
+__device__ __forceinline__ double quick_div(double a, double b)
+{
+    const double r = __builtin_amdgcn_rcp(b);
+    return a * fma(r, fma(-b, r, 1.0), r);
+}
+
+// The lowest root of p_k by inverse cubic interpolation from four
+// neighbouring lanes' values, lane l's point at u = l: the root in these
+// units and, as its uncertainty, how far the quadratic ones are from it.
+__device__ __forceinline__ double root_estimate(const SturmValue &s, int first, double &err)
+{
+    const int b = min(max(first - 2, 0), 60);
+    const int eb = __builtin_amdgcn_readlane(s.e, b + 1);
+    const double g = ldexp(s.f, max(min(s.e - eb, 600), -600));
+    const double f0 = lane_value(g, b), f1 = lane_value(g, b + 1), f2 = lane_value(g, b + 2), f3 = lane_value(g, b + 3);
+    // u - b = 0, 1, 2, 3
+    const double p01 = quick_div(f0, f0 - f1);
+    const double p12 = quick_div(2.0 * f1 - f2, f1 - f2);
+    const double p23 = quick_div(3.0 * f2 - 2.0 * f3, f2 - f3);
+    const double p012 = quick_div(f0 * p12 - f2 * p01, f0 - f2);
+    const double p123 = quick_div(f1 * p23 - f3 * p12, f1 - f3);
+    const double p = quick_div(f0 * p123 - f3 * p012, f0 - f3);
+    err = fmax(fabs(p - p012), fabs(p - p123));
+    return (double)b + p;
+}
+
+// ritz_min and tridiag_min_eig of gc_filter.h on one wavefront, the same
+// brackets bit for bit.  A round of 64 points takes a Sturm sequence each;
+// the values they leave give the root far beyond the next bracket
+// (root_estimate), so the brackets of the rounds to come are worked out from
+// the estimate and one more round, with their ends on its lanes, shows which
+// of them hold.  A bracket whose ends have no eigenvalue below, and one, is
+// the one that the 64 points of its round would have given.  Two to three
+// rounds in place of four to six.
+__device__ double ritz_lines(lds_cdbl2 *tri, int k, double glo, double ghi, double prev, double prev_step,
+                             double tol_rel, bool final, double &hi_out)
+{
+    constexpr int B = 64;
+    const int lane = (int)(threadIdx.x & 63);
+    double lo = glo - 1e-12 * (1.0 + fabs(glo));
+    double hi = ghi + 1e-12 * (1.0 + fabs(ghi));
+    SturmValue s = {0.0, 0, false};
+    int first = -1;           // of the last round, -1: no values to go by
+    double u0 = 0.0, du = 0.0;   // its points: u0 + du l
+    if (prev < hi) {
+        const double top = prev + 1e-12 * (1.0 + fabs(prev));
+        const double bot = top - fmax(4.0 * prev_step, 1e-9 * (1.0 + fabs(prev)));
+        if (bot > lo) {
+            const double step = (top - bot) / (double)(B - 1);
+            const double x = (lane == B - 1) ? top : bot + step * (double)lane;
+            s = sturm_value(tri, k, x);
+            const uint64_t m = __ballot(s.below);
+            first = m ? __builtin_ctzll(m) : B;
+            if (first > 0 && first < B) {
+                lo = bot + step * (double)(first - 1);
+                hi = (first == B - 1) ? top : bot + step * (double)first;
+                u0 = bot;
+                du = step;
+            } else {
+                if (first == 0) hi = bot;   // below the window: bot bounds it above
+                first = -1;
+            }
+        } else if (sturm_value(tri, k, top).below) {
+            hi = top;
+        }
+    }
+    const double width = final ? 1e-15 : 1e-2 * tol_rel;
+    // the search is over: the bracket is narrow enough, or, unless final, the
+    // convergence test fails whatever the remaining digits are
+    auto over = [&](double l, double h) __attribute__((always_inline)) {
+        if (h - l <= width * fmax(1.0, fabs(h))) return true;
+        if (!final) {
+            const double gap = prev - h, scale = fmax(1.0, fabs(h));
+            const bool fails = gap > 1e6 * tol_rel * scale;
+            const double need = (prev < INFINITY) ? 0.05 * gap : 1e-4 * scale;
+            if (fails && h - l <= need) return true;
+        }
+        return false;
+    };
+    int round = 0;
+    while (round < 24 && !over(lo, hi)) {
+        if (first >= 0 && !final) {
+            double err;
+            const double u = root_estimate(s, first, err);
+            const double r = fma(du, u, u0), unsure = 4.0 * du * err;
+            // the brackets of the rounds to come, one per pair of lanes
+            double pl = lo, ph = hi, x = lo;
+            int n = 0;
+            while (n < 16 && round + n < 24 && !over(pl, ph)) {
+                const double step = (ph - pl) / (double)(B + 1);
+                const double q = (r - pl) / step;
+                // the estimate has to tell the round's points apart
+                if (!(unsure < 0.25 * step) || !(q >= -1.0 && q <= (double)(B + 2))) break;
+                const int f = min(max((int)floor(q), 0), B);
+                const double nlo = (f == 0) ? pl : pl + step * (double)f;
+                const double nhi = (f == B) ? ph : pl + step * (double)(f + 1);
+                pl = nlo;
+                ph = nhi;
+                x = (lane == 2 * n) ? pl : (lane == 2 * n + 1) ? ph : x;
+                ++n;
+            }
+            if (n > 0) {
+                const uint64_t m = __ballot(sturm_value(tri, k, x).below);
+                // pairs (0, 1) from the first on
+                int ok = 0;
+                while (ok < n && ((m >> (2 * ok)) & 3ull) == 2ull) ++ok;
+                // replay the brackets that hold
+                for (int i = 0; i < ok; ++i) {
+                    lo = lane_value(x, 2 * i);
+                    hi = lane_value(x, 2 * i + 1);
+                }
+                round += ok;
+                first = -1;
+                if (ok == n) continue;
+            }
+            if (round >= 24 || over(lo, hi)) break;
+        }
+        const double step = (hi - lo) / (double)(B + 1);
+        const double x = lo + step * (double)(lane + 1);
+        s = sturm_value(tri, k, x);
+        const uint64_t m = __ballot(s.below);
+        first = m ? __builtin_ctzll(m) : B;
+        const double nlo = (first == 0) ? lo : lo + step * (double)first;
+        const double nhi = (first == B) ? hi : lo + step * (double)(first + 1);
+        u0 = lo + step;
+        du = step;
+        lo = nlo;
+        hi = nhi;
+        ++round;
+    }
+    hi_out = hi;
+    return 0.5 * (lo + hi);
+}
+
+// The Ritz value of a check, computed by the first wavefront alone and
+// handed to the others through LDS.  The workgroup synchronises before (the
+// tridiagonal is complete in LDS) and after.
 template <int B>
-__device__ double ritz_wave0(lds_cdouble *alpha, lds_cdouble *beta2, int k, double glo, double ghi, double prev,
-                             double prev_step, int *ired, int &iph, bool final, double &hi_out, double *share)
+__device__ double ritz_wave0(lds_ptr<dbl2> tri, int k, double glo, double ghi, double prev, double prev_step,
+                             bool final, double &hi_out, double *share)
 {
     if (B > 64) __syncthreads();
     else wave_sync();
     double theta = 0.0, hi = 0.0;
     if (B == 64 || threadIdx.x < 64) {
-        theta = ritz_min<64>(alpha, beta2, k, glo, ghi, prev, prev_step, ired, iph, kRitzTol, final, hi);
+        if ((threadIdx.x & 63) < kTriPad) tri[k + (int)(threadIdx.x & 63)] = dbl2{64.0, 0.0};
+        wave_sync();
+        theta = ritz_lines((lds_cdbl2 *)tri, k, glo, ghi, prev, prev_step, kRitzTol, final, hi);
         if (B > 64 && threadIdx.x == 0) {
             share[0] = theta;
             share[1] = hi;
@@ -35,6 +229,46 @@ __device__ double ritz_wave0(lds_cdouble *alpha, lds_cdouble *beta2, int k, doub
     return theta;
 }
 
+// Four sums over the workgroup, each with the additions of wg_sum_n
+// (gc_filter.h) in the same order.  Two steps inside a quad halve the values
+// a lane carries (it passes on the ones it gives up), so the four steps that
+// remain move one value and not four: 35 vector instructions against 80.
+// Lane l ends with the sum of class (l & 3), reversed in odd quads, where the
+// mirror steps then find the same class.
+template <int B> __device__ __forceinline__ void wg_sum4(double (&v)[4], double *red, int &ph)
+{
+    const int lane = (int)(threadIdx.x & 63);
+    const bool c1 = ((lane ^ (lane >> 2)) & 1) != 0, c2 = (((lane >> 1) ^ (lane >> 2)) & 1) != 0;
+    double x[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const double keep = c1 ? v[2 * n + 1] : v[2 * n], give = c1 ? v[2 * n] : v[2 * n + 1];
+        x[n] = keep + dpp64<kDppQuadSwap1>(give);
+    }
+    const double keep = c2 ? x[1] : x[0], give = c2 ? x[0] : x[1];
+    double y = keep + dpp64<kDppQuadSwap2>(give);
+    y += dpp64<kDppHalfMirror>(y);
+    y += dpp64<kDppRowMirror>(y);
+    RowPair p = row_pair<16>(y);
+    y = p.lo + p.hi;
+    p = row_pair<32>(y);
+    y = p.lo + p.hi;
+    if (B > 64) {
+        // lane l adds up the wavefronts' sums of class (l & 3)
+        constexpr int W = B / 64;
+        double *r = red + ph * (4 * W);
+        ph ^= 1;
+        if (lane < 4) r[lane * W + (threadIdx.x >> 6)] = y;
+        __syncthreads();
+        const double *rl = r + (lane & 3) * W;
+        y = rl[0];
+#pragma unroll
+        for (int w = 1; w < W; ++w) y += rl[w];
+    }
+#pragma unroll
+    for (int n = 0; n < 4; ++n) v[n] = lane_value(y, n);
+}
+
 // FP filter in the line-segment layout, one workgroup of B threads per copy
 // of the compacted tables (at the copy's representative start): thread t
 // owns S consecutive sites along direction 0 (x_0 runs fastest, so they are
@@ -45,23 +279,47 @@ __device__ double ritz_wave0(lds_cdouble *alpha, lds_cdouble *beta2, int k, doub
 // threads, the forward link weights of directions 1..d-1 (and of direction
 // 0 when a line has several segments), S P doubles each, and the
 // tridiagonal.  LDS arrays are segment-major with a compile-time stride P
-// (B, or 7B/8 when the launch's T = V/S threads fit in it): the k-th site
-// of thread t's segment sits at k P + t, so the threads of a wavefront
-// touch consecutive doubles, a neighbour in direction mu >= 1 (the same k
-// of another segment) sits at a constant thread offset, and every site's
-// address is a per-thread base plus a compile-time offset.  FORM bit 0:
-// the segments are whole lines (S == N0); bit 1: P = 7B/8.  The iteration is
-// post_kernel's: one reduction per iteration, the same formulas per site.
+// (B, or 7B/8 when the launch's T = V/S threads fit in it), two sites of a
+// thread side by side: sites k and k + 1 (k even) of thread t's segment sit
+// at k P + 2 t, the last of an odd segment at (S - 1) P + t.  A wavefront
+// touches consecutive pairs, one 16-byte access each (217 bytes per clock of
+// a CU against 118 in 8-byte accesses), a neighbour in direction mu >= 1
+// (the same k of another segment) sits at a constant thread offset, and every
+// site's address is one of 2 d per-thread bases plus a compile-time offset.
+// FORM bit 0: the segments are whole lines (S == N0); bit 1: P = 7B/8.  The
+// iteration is post_kernel's: one reduction per iteration, the same formulas
+// per site.
+//
+// Per iteration LDS moves 4 (d - 1) + 1 values per site, 50 KB on 6^4, and the
+// reduction's and the checks' latency comes on top; several workgroups per
+// CU hide it, as many as registers and LDS allow.  Copies filtered, before
+// and after pairs, wg_sum4 and ritz_lines: 100000 on 6^4 38.8 -> 31.0 ms,
+// 100000 on 10^3 25.9 -> 21.1, 10000 on 9^3 3.08 -> 2.08, 4000 on 12^3
+// 5.07 -> 3.64, 2000 on 6^3 x 8 2.53 -> 1.85, 4000 on 32^2 2.06 -> 1.29, 20000 on 16^2
+// 1.39 -> 1.04.
+
+// Wavefronts per SIMD the filter is compiled for: five values a site in
+// registers (10 S), and addresses, scalars and loads in flight, about
+// 98 + 2 D more.  Some 15 registers over the limit of 512 / waves are spilled
+// outside the iteration and cost less than the wavefront: 10000 copies on 9^3
+// (S = 3) take 2.08 ms with four wavefronts and 2.32 with three, 36000 on
+// 8^3 (S = 8) 3.03 with three and 3.12 with two.  512 threads are two
+// wavefronts on each SIMD: two or four (3 x 21 x 21: 3.87 and 2.54 ms).
+constexpr int lanczos_waves(int B, int S, int D)
+{
+    const int regs = 10 * S + 2 * D + 98;
+    return regs <= 142 ? 4 : regs <= 186 && B < 512 ? 3 : 2;
+}
+
 template <int B, int S, int D, int FORM>
-__global__ __launch_bounds__(B) void lanczos_kernel(const GcJobDev *__restrict__ jobs, int n_jobs,
+__global__ __launch_bounds__(B, lanczos_waves(B, S, D)) void lanczos_kernel(const GcJobDev *__restrict__ jobs, int n_jobs,
                                                     unsigned long long *next)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double red[2 * 4 * (B / 64)];
-    __shared__ int ired[2 * (B / 64)];
     __shared__ double ritz[2];
     __shared__ unsigned long long claim;
-    int rph = 0, iph = 0;   // halves of the reduction scratch in use
+    int rph = 0;   // half of the reduction scratch in use
     for (;;) {
         const int tid = (int)threadIdx.x + opaque_zero();
         if (tid == 0) claim = atomicAdd(next, 1ULL);
@@ -87,11 +345,14 @@ __global__ __launch_bounds__(B) void lanczos_kernel(const GcJobDev *__restrict__
         const int nw = whole ? d - 1 : d;   // weight arrays in LDS
         const int w0off = whole ? -1 : 0;   // LDS array of direction mu: mu + w0off
         constexpr int A = S * P;            // doubles per LDS array
+        // place of the k-th site of thread t's segment in an LDS array
+        auto at = [&](int k, int t) __attribute__((always_inline)) {
+            return k < 2 * (S / 2) ? 2 * ((k >> 1) * P + t) + (k & 1) : k * P + t;
+        };
         lds_ptr<double> u = as_lds(reinterpret_cast<double *>(smem));
         lds_ptr<double> wl = u + A;
         const int lmax = min(min(J.lanczos_max, GC_LMAX), V);
-        lds_ptr<double> alpha = wl + (size_t)nw * A;
-        lds_ptr<double> beta2 = alpha + lmax;
+        lds_ptr<dbl2> tri = (lds_ptr<dbl2>)(wl + (size_t)nw * A);
 
         // own link weights w = Re(conj(g_i) U_{i,mu} g_{i+mu}) from the
         // representative's state in global memory: direction 0 into
@@ -125,7 +386,7 @@ __global__ __launch_bounds__(B) void lanczos_kernel(const GcJobDev *__restrict__
                         const double tr = uu.x * gf.x - uu.y * gf.y, ti = uu.x * gf.y + uu.y * gf.x;
                         const double ur = gi.x * tr + gi.y * ti;
                         if (mu == 0) w0[k] = ur;
-                        if (mu + w0off >= 0) wl[(mu + w0off) * A + k * P + tid] = ur;
+                        if (mu + w0off >= 0) wl[(mu + w0off) * A + at(k, tid)] = ur;
                     }
                 }
             }
@@ -151,7 +412,7 @@ __global__ __launch_bounds__(B) void lanczos_kernel(const GcJobDev *__restrict__
         for (int k = 0; k < S; ++k) {
             if (act) {
                 uo[k] -= mean;
-                u[k * P + tid] = uo[k];
+                u[at(k, tid)] = uo[k];
             }
         }
         const double sigma = 4.0 * d + 1.0;
@@ -164,25 +425,16 @@ __global__ __launch_bounds__(B) void lanczos_kernel(const GcJobDev *__restrict__
         bool conv = false;
         // the neighbours across the ends of a segment that is not a whole
         // line: the first site of the next segment, the last of the previous
-        const int ia = line * nseg + ((o + S) % N0) / S;
-        const int ib = (S - 1) * P + line * nseg + ((o + N0 - 1) % N0) / S;
-        // byte offsets from u of the four values a site reads per direction
-        // mu >= 1 (fixed for the copy): the own forward weight (aw), the
-        // forward neighbour's u (af), the backward neighbour's weight (bw)
-        // and u (bu); the k-th site adds a compile-time offset.  Each is its
-        // own register, opaque to the compiler: two loads from one register
-        // would be paired into a ds_read2st64, whose two addresses, a
-        // multiple of 512 bytes apart, fall in the same LDS bank.
-        lds_ptr<const unsigned char> ubase = (lds_ptr<const unsigned char>)u;
-        uint32_t aw[GC_MAXD], af[GC_MAXD], bw[GC_MAXD], bu[GC_MAXD];
+        const int ia = at(0, line * nseg + ((o + S) % N0) / S);
+        const int ib = at(S - 1, line * nseg + ((o + N0 - 1) % N0) / S);
+        // byte offsets of pair 0 in LDS: the thread's, and its neighbours'
+        lds_ptr<unsigned char> u8 = (lds_ptr<unsigned char>)u;
+        const uint32_t t16 = 16u * (uint32_t)tid;
+        uint32_t f16[GC_MAXD], b16[GC_MAXD];
 #pragma unroll
         for (int mu = 0; mu < GC_MAXD; ++mu) {
-            const uint32_t warr = 8u * (uint32_t)((1 + mu + w0off) * A);   // the weight array of mu
-            aw[mu] = warr + 8u * (uint32_t)tid;
-            af[mu] = 8u * (uint32_t)(tid + df[mu]);
-            bw[mu] = warr + 8u * (uint32_t)(tid + db[mu]);
-            bu[mu] = 8u * (uint32_t)(tid + db[mu]);
-            if (mu > 0 && mu < d) asm volatile("" : "+v"(aw[mu]), "+v"(af[mu]), "+v"(bw[mu]), "+v"(bu[mu]));
+            f16[mu] = 16u * (uint32_t)(tid + df[mu]);
+            b16[mu] = 16u * (uint32_t)(tid + db[mu]);
         }
         // the diagonal of M at the own sites, the sum of their 2d link
         // weights, once per copy (M u)_i = diag_i u_i - sum_nb w u_nb
@@ -197,8 +449,8 @@ __global__ __launch_bounds__(B) void lanczos_kernel(const GcJobDev *__restrict__
 #pragma unroll
                 for (int mu = 1; mu < GC_MAXD; ++mu)
                     if (mu < d) {
-                        lds_ptr<const double> wm = wl + (mu + w0off) * A + k * P;
-                        a += wm[tid] + wm[tid + db[mu]];
+                        lds_ptr<const double> wm = wl + (mu + w0off) * A;
+                        a += wm[at(k, tid)] + wm[at(k, tid + db[mu])];
                     }
                 dg[k] = act ? a : 0.0;
             }
@@ -218,52 +470,72 @@ __global__ __launch_bounds__(B) void lanczos_kernel(const GcJobDev *__restrict__
                     ub = u[ib];
                     wbe = wl[ib];
                 }
+                // two sites at a time, their values side by side in LDS
 #pragma unroll
-                for (int k = 0; k < S; ++k) {
-                    const uint32_t kb = 8u * (uint32_t)(k * P);
-                    const double ui = uo[k];
-                    // direction 0: neighbours and weights of the own segment
-                    const double uf = (k + 1 < S) ? uo[k + 1] : ua;
-                    const double ubk = (k > 0) ? uo[k - 1] : ub;
-                    const double wb0 = (k > 0) ? w0[k - 1] : wbe;
-                    double m = dg[k] * ui;
-                    m = fma(-w0[k], uf, m);
-                    m = fma(-wb0, ubk, m);
+                for (int k0 = 0; k0 < S; k0 += 2) {
+                    const int n = k0 + 1 < S ? 2 : 1;
+                    double m[2];
+#pragma unroll
+                    for (int h = 0; h < n; ++h) {
+                        // direction 0: neighbours and weights of the own segment
+                        const int k = k0 + h;
+                        m[h] = dg[k] * uo[k];
+                        m[h] = fma(-w0[k], (k + 1 < S) ? uo[k + 1] : ua, m[h]);
+                        m[h] = fma(-((k > 0) ? w0[k - 1] : wbe), (k > 0) ? uo[k - 1] : ub, m[h]);
+                    }
 #pragma unroll
                     for (int mu = 1; mu < GC_MAXD; ++mu)
                         if (mu < d) {
-                            lds_ptr<const unsigned char> b8 = ubase + kb;
-                            const double wf_ = *(lds_ptr<const double>)(b8 + aw[mu]);
-                            const double uf_ = *(lds_ptr<const double>)(b8 + af[mu]);
-                            const double wb_ = *(lds_ptr<const double>)(b8 + bw[mu]);
-                            const double ub_ = *(lds_ptr<const double>)(b8 + bu[mu]);
-                            m = fma(-wf_, uf_, m);
-                            m = fma(-wb_, ub_, m);
+                            // the pair's place is a constant from the
+                            // thread's; a last single site's likewise from
+                            // half of it
+                            const uint32_t w8 = 8u * (uint32_t)((1 + mu + w0off) * A);
+                            if (n == 2) {
+                                const uint32_t kb = 16u * (uint32_t)((k0 >> 1) * P);
+                                const dbl2 wf = *(lds_ptr<const dbl2>)(u8 + t16 + (w8 + kb));
+                                const dbl2 uf = *(lds_ptr<const dbl2>)(u8 + f16[mu] + kb);
+                                const dbl2 wb = *(lds_ptr<const dbl2>)(u8 + b16[mu] + (w8 + kb));
+                                const dbl2 ub2 = *(lds_ptr<const dbl2>)(u8 + b16[mu] + kb);
+                                m[0] = fma(-wf.x, uf.x, m[0]);
+                                m[1] = fma(-wf.y, uf.y, m[1]);
+                                m[0] = fma(-wb.x, ub2.x, m[0]);
+                                m[1] = fma(-wb.y, ub2.y, m[1]);
+                            } else {
+                                const uint32_t kb = 8u * (uint32_t)(k0 * P);
+                                const double wf = *(lds_ptr<const double>)(u8 + (t16 >> 1) + (w8 + kb));
+                                const double uf = *(lds_ptr<const double>)(u8 + (f16[mu] >> 1) + kb);
+                                const double wb = *(lds_ptr<const double>)(u8 + (b16[mu] >> 1) + (w8 + kb));
+                                const double ub2 = *(lds_ptr<const double>)(u8 + (b16[mu] >> 1) + kb);
+                                m[0] = fma(-wf, uf, m[0]);
+                                m[0] = fma(-wb, ub2, m[0]);
+                            }
                         }
-                    mv[k] = m;
-                    s4[0] += ui * ui;
-                    s4[1] += ui * m;
-                    s4[2] += ui;
-                    s4[3] += ui * qp[k];
-                    // one site at a time: bounds the loads in flight
+#pragma unroll
+                    for (int h = 0; h < n; ++h) {
+                        const int k = k0 + h;
+                        mv[k] = m[h];
+                        s4[0] += uo[k] * uo[k];
+                        s4[1] += uo[k] * m[h];
+                        s4[2] += uo[k];
+                        s4[3] += uo[k] * qp[k];
+                    }
+                    // bounds the loads in flight
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
-            wg_sum_n<B, 4>(s4, red, rph);
+            wg_sum4<B>(s4, red, rph);
             // 1/|u| from the reciprocal square root, no division on the
             // iteration's dependency chain (a vanishing |u| gives bt = 0)
             const double inv = rsq(fmax(s4[0], 1e-300));
             const double bt = s4[0] * inv;
             const double bp = it > 0 ? bt : 0.0;      // beta_{j-1} (the start vector's norm is not in T)
             if (it > 0) {
-                if (tid == 0) beta2[it - 1] = s4[0];
                 rows_lo = fmin(rows_lo, a_prev - b_prev2 - bt);
                 rows_hi = fmax(rows_hi, a_prev + b_prev2 + bt);
                 if (bt <= 1e-13 * sigma) {
                     // the Krylov space is exhausted: T of it rows is exact
                     double theta_hi;
-                    theta = ritz_wave0<B>(alpha, beta2, it, rows_lo, rows_hi, theta_old, theta_step, ired, iph, true,
-                                          theta_hi, ritz);
+                    theta = ritz_wave0<B>(tri, it, rows_lo, rows_hi, theta_old, theta_step, true, theta_hi, ritz);
                     conv = true;
                     break;
                 }
@@ -271,7 +543,7 @@ __global__ __launch_bounds__(B) void lanczos_kernel(const GcJobDev *__restrict__
             const double sq = s4[2] * inv;
             const double shift = sigma_v * sq;
             const double a_j = s4[1] * inv * inv + shift * sq - bp * (s4[3] * inv);
-            if (tid == 0) alpha[it] = a_j;
+            if (tid == 0) tri[it] = dbl2{a_j, it > 0 ? s4[0] : 0.0};
             if (act) {
 #pragma unroll
                 for (int k = 0; k < S; ++k) {
@@ -279,14 +551,18 @@ __global__ __launch_bounds__(B) void lanczos_kernel(const GcJobDev *__restrict__
                     const double r = mv[k] * inv + shift - bp * qp[k] - a_j * q;
                     qp[k] = q;
                     uo[k] = r;
-                    u[k * P + tid] = r;
+                }
+#pragma unroll
+                for (int k = 0; k < S; k += 2) {
+                    if (k + 1 < S) *(lds_ptr<dbl2>)(u8 + t16 + 16u * (uint32_t)((k >> 1) * P)) = dbl2{uo[k], uo[k + 1]};
+                    else *(lds_ptr<double>)(u8 + (t16 >> 1) + 8u * (uint32_t)(k * P)) = uo[k];
                 }
             }
             if (it + 1 >= next_check || it + 1 == lmax) {
                 const bool final = it + 1 == lmax;
                 double theta_hi;
-                theta = ritz_wave0<B>(alpha, beta2, it + 1, fmin(rows_lo, a_j - bp), fmax(rows_hi, a_j + bp),
-                                      theta_old, theta_step, ired, iph, final, theta_hi, ritz);
+                theta = ritz_wave0<B>(tri, it + 1, fmin(rows_lo, a_j - bp), fmax(rows_hi, a_j + bp), theta_old,
+                                      theta_step, final, theta_hi, ritz);
                 const double tol = kRitzTol * fmax(1.0, fabs(theta));
                 const double change = theta_old - theta;
                 if (fabs(change) <= tol) {

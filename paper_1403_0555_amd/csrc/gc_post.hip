@@ -826,7 +826,7 @@ size_t gc_lanczos_lds_bytes(int d, int N0, int S, int V, int lmax, int block)
     const int nw = (S == N0) ? d - 1 : d;
     const int P = (gc_lanczos_form(N0, S, V, block) & 2) ? 7 * block / 8 : block;
     const size_t l = (size_t)std::min(std::min(lmax, GC_LMAX), V);
-    return 8 * (size_t)(1 + nw) * S * P + 16 * l;
+    return 8 * (size_t)(1 + nw) * S * P + 16 * (l + GC_TRI_PAD);
 }
 
 #define GC_LANCZOS_DECLARE_DIM(D)                                                                         \

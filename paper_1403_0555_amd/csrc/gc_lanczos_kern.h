@@ -320,6 +320,10 @@ __global__ __launch_bounds__(B, lanczos_waves(B, S, D)) void lanczos_kernel(cons
     __shared__ double ritz[2];
     __shared__ unsigned long long claim;
     int rph = 0;   // half of the reduction scratch in use
+    // copies filtered and not yet in their job's counter; copies come in job
+    // order
+    uint32_t runs = 0;
+    int runs_job = 0;
     for (;;) {
         const int tid = (int)threadIdx.x + opaque_zero();
         if (tid == 0) claim = atomicAdd(next, 1ULL);
@@ -330,6 +334,11 @@ __global__ __launch_bounds__(B, lanczos_waves(B, S, D)) void lanczos_kernel(cons
         uint64_t c;
         copy_item(jobs, n_jobs, s, jn, c);
         jn = uniform(jn);
+        if (jn != runs_job) {
+            if (tid == 0 && runs) atomicAdd(&jobs[runs_job].cnt->lanczos_runs, (unsigned long long)runs);
+            runs = 0;
+            runs_job = jn;
+        }
         if (jn < 0) break;
         const GcJobDev &J = jobs[jn];
         const GcOrbitDev &O = J.orb;
@@ -582,7 +591,10 @@ __global__ __launch_bounds__(B, lanczos_waves(B, S, D)) void lanczos_kernel(cons
         if (!conv) flags |= GC_F_LANCZOS_CAP;
         if (tid == 0) {
             write_filter(J, c, local, theta, flags, (uint32_t)it);
-            atomicAdd(&J.cnt->lanczos_runs, 1ULL);
+            if (++runs == 16) {
+                atomicAdd(&J.cnt->lanczos_runs, 16ULL);
+                runs = 0;
+            }
         }
         __syncthreads();
     }

@@ -138,6 +138,8 @@ __global__ __launch_bounds__(B) void relax_wg_kernel(const GcJobDev *__restrict_
     __shared__ double red[B / 64];
     __shared__ unsigned long long claim;
     const int tid = threadIdx.x;
+    RelaxTally tally = {0, 0, 0};
+    int tally_job = 0;   // starts are claimed in job order
     for (;;) {
         if (tid == 0) claim = atomicAdd(next, 1ULL);
         __syncthreads();
@@ -147,6 +149,10 @@ __global__ __launch_bounds__(B) void relax_wg_kernel(const GcJobDev *__restrict_
         int jn = 0;
         while (jn + 1 < n_jobs && prefix[jn + 1] <= s) ++jn;
         jn = uniform(jn);
+        if (jn != tally_job) {
+            if (tid == 0) flush_tally(jobs[tally_job], tally);
+            tally_job = jn;
+        }
         const GcJobDev &J = jobs[jn];
         const GcOrbitDev &O = J.orb;
         const int V = O.V;
@@ -197,9 +203,10 @@ __global__ __launch_bounds__(B) void relax_wg_kernel(const GcJobDev *__restrict_
         dbl2 *out = reinterpret_cast<dbl2 *>(J.states + local * (uint64_t)V);
         for (int i = tid; i < V; i += B)
             out[i] = in64 ? st64[i] : dbl2{(double)st32[i].x, (double)st32[i].y};
-        if (tid == 0) record_relax(J, local, status, sw32, sw64, D);
+        if (tid == 0) record_relax(J, local, status, sw32, sw64, D, tally);
         __syncthreads();
     }
+    if (tid == 0) flush_tally(jobs[tally_job], tally);
 }
 
 }  // namespace

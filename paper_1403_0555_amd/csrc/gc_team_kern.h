@@ -93,6 +93,7 @@ template <int M> struct TeamShared {
     uint32_t born[M], end[M];      // the team's sweep count at its begin and at its cap
     uint32_t near;                 // starts that may have stopped (none in most sweeps)
     int32_t spare;                 // a start is claimed ahead
+    RelaxTally tally;
 };
 
 template <int D, int K, int SPT, int M, int MAXW, int PF, typename R, bool RELAX, bool MAXABS>
@@ -293,7 +294,7 @@ __device__ __forceinline__ void team_job(const GcJobDev &J, unsigned long long *
                     J.rec[loc] = r;
                 } else {
                     const uint32_t sw32 = from32 ? J.rec[loc].sweeps32 : 0u;
-                    record_relax(J, loc, status, F32 ? sweeps : sw32, F32 ? 0 : sweeps, sh.D[m]);
+                    record_relax(J, loc, status, F32 ? sweeps : sw32, F32 ? 0 : sweeps, sh.D[m], sh.tally);
                 }
             }
         }
@@ -346,7 +347,10 @@ __device__ __forceinline__ void team_job(const GcJobDev &J, unsigned long long *
         __syncthreads();
     };
 
-    if (tid == 0) sh.near = 0;
+    if (tid == 0) {
+        sh.near = 0;
+        sh.tally = RelaxTally{0, 0, 0};
+    }
     refill();
     if constexpr (K == 2) {
         // a sweep: colour 0, barrier, colour 1, barrier.  The norm of the
@@ -450,6 +454,7 @@ __device__ __forceinline__ void team_job(const GcJobDev &J, unsigned long long *
             if (__builtin_expect((!exhausted || spare) && act != all, 0)) refill();
         }
     }
+    if (tid == 0) flush_tally(J, sh.tally);
 }
 
 // Workgroups move from job to job of the launch as their starts run out.

@@ -266,7 +266,7 @@ __device__ int relax_wave(const GcJobDev &J, const GcWaveOrbit &WO, CP coef, lds
 template <int D, int NS, int CREG, int WPS, typename CP64, typename CP32>
 __device__ void relax_start_wave(const GcJobDev &J, const GcWaveOrbit &WO, CP64 coef64, CP32 coef32,
                                  lds_ptr<const u32x4> nbt, lds_ptr<dbl2> st64, lds_ptr<flt2> st32,
-                                 glb_ptr<flt2> bounce, uint64_t local, double *red)
+                                 glb_ptr<flt2> bounce, uint64_t local, double *red, RelaxTally &tally)
 {
     constexpr int T = 64 * WPS;   // threads on the start
     const int lane = WPS > 1 ? (int)threadIdx.x : (int)(threadIdx.x & 63);
@@ -328,7 +328,7 @@ __device__ void relax_start_wave(const GcJobDev &J, const GcWaveOrbit &WO, CP64 
         const int p = WO.loc[i];
         out[i] = in64 ? st64[p] : dbl2{(double)st32[p].x, (double)st32[p].y};
     }
-    if (lane == 0) record_relax(J, local, status, sw32, sw64, Dn);
+    if (lane == 0) record_relax(J, local, status, sw32, sw64, Dn, tally);
     start_sync<WPS>();
 }
 
@@ -391,18 +391,30 @@ __global__ __launch_bounds__(64 * WAVES) void wave_kernel(const GcJobDev *__rest
         lds_ptr<flt2> st32 = as_lds(reinterpret_cast<flt2 *>(smem + off + (size_t)wave * 16 * V));
         glb_ptr<flt2> bounce =
             as_global(reinterpret_cast<flt2 *>(bounce_all) + ((uint64_t)blockIdx.x * WAVES + wave) * (uint64_t)vmax);
+        // Starts are claimed a few at a time, fewer towards the end of the
+        // job: a claim is an atomic that all wavefronts wait for in turn.
+        const uint64_t n_starts = J.n_starts, waves = (uint64_t)gridDim.x * WAVES;
+        RelaxTally tally = {0, 0, 0};
+        uint64_t s = 0, end = 0;
         for (;;) {
-            unsigned long long s = 0;
-            if (lane == 0) s = atomicAdd(&job_next[jn], 1ULL);
-            s = uniform((uint64_t)s);
-            if (s >= J.n_starts) break;
+            if (s == end) {
+                const uint64_t left = n_starts - min(end, n_starts);
+                const uint64_t chunk = max((uint64_t)1, min((uint64_t)8, left / (4 * waves)));
+                unsigned long long c = 0;
+                if (lane == 0) c = atomicAdd(&job_next[jn], (unsigned long long)chunk);
+                s = uniform((uint64_t)c);
+                if (s >= n_starts) break;
+                end = min(s + chunk, n_starts);
+            }
             lds_ptr<const u32x4> nbc = nbt;
             if (COEF_LDS)
-                relax_start_wave<D, NS, CREG, 1>(J, WO, c64, c32, nbc, st64, st32, bounce, s, nullptr);
+                relax_start_wave<D, NS, CREG, 1>(J, WO, c64, c32, nbc, st64, st32, bounce, s, nullptr, tally);
             else
                 relax_start_wave<D, NS, CREG, 1>(J, WO, as_global(g64), as_global(g32), nbc, st64, st32, bounce, s,
-                                                 nullptr);
+                                                 nullptr, tally);
+            ++s;
         }
+        if (lane == 0) flush_tally(J, tally);
         __syncthreads();
         j0 = jn;
     }
@@ -452,14 +464,17 @@ __global__ __launch_bounds__(64 * WPS) void wps_kernel(const GcJobDev *__restric
         const dbl2 *g64 = reinterpret_cast<const dbl2 *>(WO.coef64);
         const flt2 *g32 = reinterpret_cast<const flt2 *>(WO.coef32);
         lds_ptr<const u32x4> nbc = nbt;
+        RelaxTally tally = {0, 0, 0};
         for (;;) {
             if (threadIdx.x == 0) claim = atomicAdd(&job_next[jn], 1ULL);
             __syncthreads();
             const uint64_t s = uniform((uint64_t)claim);
             __syncthreads();
             if (s >= J.n_starts) break;
-            relax_start_wave<D, 2, 0, WPS>(J, WO, as_global(g64), as_global(g32), nbc, st64, st32, bounce, s, red);
+            relax_start_wave<D, 2, 0, WPS>(J, WO, as_global(g64), as_global(g32), nbc, st64, st32, bounce, s, red,
+                                        tally);
         }
+        if (threadIdx.x == 0) flush_tally(J, tally);
         __syncthreads();
         j0 = jn;
     }

@@ -5,9 +5,11 @@
 
 // An instantiation: spt sites of each colour per thread, m starts in step, at
 // most maxw wavefronts per workgroup, compiled for minw wavefronts per SIMD
-// (512 / minw registers), pf neighbours fetched ahead.
+// (512 / minw registers), pf neighbours fetched ahead; lone: a start left on
+// its own has a loop of its own, in double precision.
 struct GcTeamClass {
     int spt, m, maxw, minw, pf;
+    bool lone;
 };
 
 // Classes by dimension and colours.  The links and neighbour offsets of a
@@ -22,22 +24,29 @@ struct GcTeamClass {
 // 1.6 against 10.8, 9^3 2.0 against 6.0.  The clock falls from 2.2 to 1.9 GHz
 // as the vector units fill: the power limit takes part of what a better
 // overlap would give.
+// The lone starts' loop costs the main one some registers: none where there
+// are enough, but with it 200 sweeps of 5 10^4 starts of 10^3 took 30.0 ms
+// (23.8), of 2 10^4 of 12^3 22.2 (18.8) and of 3 10^4 of 6^4 27.9 (26.5), so
+// those classes do without (single precision has room in all).
 constexpr GcTeamClass gc_team_class(int d, int K, int cls)
 {
     if (K == 2) {
         if (d <= 2)
-            return cls == 1 ? GcTeamClass{1, 3, 4, 4, 2 * d} : cls == 2 ? GcTeamClass{1, 3, 8, 4, 2 * d}
-                                                                        : GcTeamClass{1, 3, 16, 4, 2 * d};
+            return cls == 1   ? GcTeamClass{1, 3, 4, 4, 2 * d, true}
+                   : cls == 2 ? GcTeamClass{1, 3, 8, 4, 2 * d, true}
+                              : GcTeamClass{1, 3, 16, 4, 2 * d, true};
         if (d == 3)
-            return cls == 1 ? GcTeamClass{1, 3, 4, 3, 4} : cls == 2 ? GcTeamClass{1, 3, 8, 4, 1}
-                                                                    : GcTeamClass{1, 3, 16, 4, 1};
-        return cls == 1 ? GcTeamClass{1, 3, 4, 3, 0}
-                        : cls == 2 ? GcTeamClass{1, 7, 8, 2, 4}
-                                   : cls == 3 ? GcTeamClass{1, 3, 12, 3, 1} : GcTeamClass{2, 3, 8, 2, 1};
+            return cls == 1   ? GcTeamClass{1, 3, 4, 3, 4, true}
+                   : cls == 2 ? GcTeamClass{1, 3, 8, 4, 1, false}
+                              : GcTeamClass{1, 3, 16, 4, 1, false};
+        return cls == 1   ? GcTeamClass{1, 3, 4, 3, 0, true}
+               : cls == 2 ? GcTeamClass{1, 7, 8, 2, 4, true}
+               : cls == 3 ? GcTeamClass{1, 3, 12, 3, 1, false}
+                          : GcTeamClass{2, 3, 8, 2, 1, false};
     }
-    if (K == 3 && d == 2) return cls == 1 ? GcTeamClass{1, 3, 4, 4, 0} : GcTeamClass{1, 3, 8, 4, 0};
-    if (K == 3 && d == 3) return cls == 1 ? GcTeamClass{1, 3, 4, 3, 0} : GcTeamClass{1, 3, 8, 2, 0};
-    return GcTeamClass{1, 3, 8, 2, 0};
+    if (K == 3 && d == 2) return cls == 1 ? GcTeamClass{1, 3, 4, 4, 0, true} : GcTeamClass{1, 3, 8, 4, 0, true};
+    if (K == 3 && d == 3) return cls == 1 ? GcTeamClass{1, 3, 4, 3, 0, true} : GcTeamClass{1, 3, 8, 2, 0, true};
+    return GcTeamClass{1, 3, 8, 2, 0, true};
 }
 
 // Shape of the team kernel for a lattice: its class (0: none, the other relax

@@ -56,3 +56,22 @@ def test_refilled_places_do_not_depend_on_the_launch(ctx, extent, n, precision):
         assert np.array_equal(many[f][few:], last[f]), f
     ctx.gc_release(h)
     ctx.gc_release(h2)
+
+
+@pytest.mark.parametrize("extent", [(16, 16), (32, 32), (8, 8, 8), (4, 4, 4, 4), (4, 6, 6, 6), (9, 15), (3, 3, 3, 3),
+                                    (9, 9, 9), (5, 5, 5)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_a_start_on_its_own_stops_at_its_sweep(ctx, extent, precision):
+    """A start that a workgroup holds alone runs several sweeps between looks
+    at its norms: every cap, and every sweep that converges, is found."""
+    phi = GI.orbit_angles(extent, 6, 0)
+    for k, kw in enumerate([{"max_sweeps": c} for c in range(1, 9)] +
+                           [{"eps64": e, "eps32": 10 * e} for e in (3e-2, 1e-2, 3e-3, 1e-3, 3e-4, 1e-5)]):
+        p = gc.SolveParams(omega=1.7, precision=precision, first_start=11 * k, **kw)
+        h, _, starts, _ = run_gpu(ctx, extent, phi, 3, p)
+        rec, _, _ = O.solve(extent, phi, 11 * k + np.arange(3), oracle_params(p))
+        assert np.array_equal(starts["status"], rec["status"])
+        assert np.max(np.abs(starts["sweeps32"].astype(np.int64) - rec["sweeps32"])) <= (precision == "mixed")
+        if precision == "fp64":
+            assert np.array_equal(starts["sweeps64"], rec["sweeps64"])
+        ctx.gc_release(h)

@@ -140,3 +140,18 @@ def test_unsupported_arguments_are_refused(ctx):
         with pytest.raises(gc.GcError) as e:
             ctx.gc_orbit_load_su2((4, 4), U, **kw)
         assert e.value.status == gc.GC_EINVAL
+
+
+@pytest.mark.parametrize("extent,seed", [((2, 32), 11), ((2, 64), 12), ((4, 34), 13), ((8, 8, 8), 14), ((12, 16, 8), 15),
+                                         ((6, 6, 6, 6), 16), ((4, 6, 8, 8), 17), ((4, 4, 10, 10), 18)])
+def test_reduction_at_the_edges_of_its_layouts(ctx, extent, seed):
+    """Links in registers up to 768 sites a colour, wavefronts full and
+    partly idle, and links from memory above."""
+    U = GI.su2_links(extent, seed, 0)
+    h, info = ctx.gc_orbit_load_su2(extent, U, max_sweeps=60)
+    phi = ctx.gc_orbit_angles(h)
+    o_phi, o_sweeps, o_R, o_conv = O.mag_project(extent, U, max_sweeps=60)
+    assert info["sweeps"] == o_sweeps and bool(info["converged"]) == bool(o_conv)
+    assert abs(info["R"] - o_R) < 1e-12
+    assert np.max(np.abs(wrapped(phi - o_phi))) < 1e-9
+    ctx.gc_release(h)

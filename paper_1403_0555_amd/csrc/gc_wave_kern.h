@@ -263,7 +263,7 @@ __device__ int relax_wave(const GcJobDev &J, const GcWaveOrbit &WO, CP coef, lds
 #undef GC_RW
 }
 
-template <int D, int NS, int CREG, int WPS, typename CP64, typename CP32>
+template <int D, int NS, int CREG, int CREG32, int WPS, typename CP64, typename CP32>
 __device__ void relax_start_wave(const GcJobDev &J, const GcWaveOrbit &WO, CP64 coef64, CP32 coef32,
                                  lds_ptr<const u32x4> nbt, lds_ptr<dbl2> st64, lds_ptr<flt2> st32,
                                  glb_ptr<flt2> bounce, uint64_t local, double *red, RelaxTally &tally)
@@ -300,7 +300,7 @@ __device__ void relax_start_wave(const GcJobDev &J, const GcWaveOrbit &WO, CP64 
     const bool fixed = (J.flags & GC_JOB_SYNC2) != 0;
     const uint64_t cap = fixed ? (uint64_t)J.fixed_sweeps[local] : J.max_sweeps;
     if (J.precision == 1) {
-        status = relax_wave<D, float, NS, CREG, WPS>(J, WO, coef32, nbt, st32, J.eps32, J.max_sweeps, false, sw32, Dn,
+        status = relax_wave<D, float, NS, CREG32, WPS>(J, WO, coef32, nbt, st32, J.eps32, J.max_sweeps, false, sw32, Dn,
                                                      red);
         if (status == GC_ST_CONVERGED) {
             // promotion g64 = normalise((double) g32): both states share the
@@ -408,9 +408,9 @@ __global__ __launch_bounds__(64 * WAVES) void wave_kernel(const GcJobDev *__rest
             }
             lds_ptr<const u32x4> nbc = nbt;
             if (COEF_LDS)
-                relax_start_wave<D, NS, CREG, 1>(J, WO, c64, c32, nbc, st64, st32, bounce, s, nullptr, tally);
+                relax_start_wave<D, NS, CREG, CREG, 1>(J, WO, c64, c32, nbc, st64, st32, bounce, s, nullptr, tally);
             else
-                relax_start_wave<D, NS, CREG, 1>(J, WO, as_global(g64), as_global(g32), nbc, st64, st32, bounce, s,
+                relax_start_wave<D, NS, CREG, CREG, 1>(J, WO, as_global(g64), as_global(g32), nbc, st64, st32, bounce, s,
                                                  nullptr, tally);
             ++s;
         }
@@ -423,7 +423,13 @@ __global__ __launch_bounds__(64 * WAVES) void wave_kernel(const GcJobDev *__rest
 // One start per workgroup of WPS wavefronts, for lattices with more than 128
 // slots per colour: each thread keeps at most two slots per colour, the
 // colour passes synchronise the workgroup.  LDS: the neighbour table (16V)
-// and one state region (16V); the coefficients are read from global memory.
+// and one state region (16V).  The coefficients come from the L2, half a
+// megabyte per sweep of 8^4 and the bound of it (5.9 us); in single precision
+// with 16 wavefronts, where 128 registers allow it, those of colour 0 (up to
+// three dimensions all) stay in registers: 10^4 mixed-precision starts of 8^4
+// 49.4 -> 45.5 ms, 5000 of 16^3 18.9 -> 17.2, 2000 of 64^2 20.9 -> 19.8.  With
+// fewer wavefronts the registers cost workgroups per CU (5000 of 4^2 x 8^2
+// 4.9 -> 7.7 ms).
 template <int D, int WPS>
 __global__ __launch_bounds__(64 * WPS) void wps_kernel(const GcJobDev *__restrict__ jobs,
                                                        const GcWaveOrbit *__restrict__ worbs, int n_jobs,
@@ -433,6 +439,7 @@ __global__ __launch_bounds__(64 * WPS) void wps_kernel(const GcJobDev *__restric
     __shared__ int cur_job;
     __shared__ unsigned long long claim;
     __shared__ double red[WPS];
+    __shared__ RelaxTally tally;   // not in registers: the sweeps have none to spare
     const int vmax = max_volume(jobs, n_jobs);
     int j0 = (int)(blockIdx.x % (unsigned)n_jobs);
     for (int round = 0; round < n_jobs; ++round) {
@@ -464,14 +471,14 @@ __global__ __launch_bounds__(64 * WPS) void wps_kernel(const GcJobDev *__restric
         const dbl2 *g64 = reinterpret_cast<const dbl2 *>(WO.coef64);
         const flt2 *g32 = reinterpret_cast<const flt2 *>(WO.coef32);
         lds_ptr<const u32x4> nbc = nbt;
-        RelaxTally tally = {0, 0, 0};
+        if (threadIdx.x == 0) tally = RelaxTally{0, 0, 0};
         for (;;) {
             if (threadIdx.x == 0) claim = atomicAdd(&job_next[jn], 1ULL);
             __syncthreads();
             const uint64_t s = uniform((uint64_t)claim);
             __syncthreads();
             if (s >= J.n_starts) break;
-            relax_start_wave<D, 2, 0, WPS>(J, WO, as_global(g64), as_global(g32), nbc, st64, st32, bounce, s, red,
+            relax_start_wave<D, 2, 0, WPS < 16 ? 0 : D <= 3 ? 2 : 1, WPS>(J, WO, as_global(g64), as_global(g32), nbc, st64, st32, bounce, s, red,
                                         tally);
         }
         if (threadIdx.x == 0) flush_tally(J, tally);

@@ -60,18 +60,17 @@ def lanczos_flops_per_site(d: int) -> int:
 # the same counter on a plain device copy of known size.  Valid only for the
 # kernel sources they were taken on (SHA-256 below); otherwise null.
 KERNEL_SOURCES = {
-    "relax": ("gc_wave_kern.h", "gc_wave.h", "gc_wave4.hip", "gc_common.h", "gc_internal.h"),
+    "relax": ("gc_team_kern.h", "gc_team.h", "gc_team_inst.h", "gc_team_d4.hip", "gc_common.h", "gc_internal.h"),
     "lanczos_kernel": ("gc_lanczos_kern.h", "gc_filter.h", "gc_lanczos4.hip", "gc_common.h", "gc_internal.h"),
 }
 TRAFFIC = {
-    # wave_rr_kernel<4, 11, 8> (exact-slot variant), 10^6 starts of the 6^4
-    # FP64 workload (one dispatch): FETCH_SIZE 665782.7 KiB x 2.0000 (a 2 GiB
-    # copy reads 1048587.5 KiB) and WRITE_SIZE 20538190.2 KiB x 1.0 (the copy
-    # writes 2097152.0 KiB); the sources have since changed in other kernels
-    # only (this kernel's assembly is unchanged)
-    "sources_sha256": "9397f846b062f06c8b80ecc8552275f05cda6f2d53713d940c0e7f84710d6c44",
+    # team_kernel<4, 2, 3, double, 0>, 10^6 starts of the 6^4 FP64 workload (one
+    # dispatch): FETCH_SIZE 10384348.0 KiB x 2.0000 (a 2 GiB copy reads
+    # 1048587.5 KiB) and WRITE_SIZE 20457932.0 KiB x 1.0 (the copy writes
+    # 2097152.0 KiB)
+    "sources_sha256": "5443afb07775f17964caf96f89cc8b820fb48ba0e4907948bb236d46f5e83ceb",
     "kernel": "relax",
-    "bytes_per_launch": 1363522944 + 21031106752,
+    "bytes_per_launch": 21267144704 + 20948922368,
 }
 
 

@@ -27,6 +27,7 @@
 #include <mutex>
 #include <string>
 #include <thread>
+#include <sys/prctl.h>
 #include <vector>
 
 // Working memory of gc_launch_static, for callers that cannot allocate: one
@@ -1318,6 +1319,8 @@ void complete_locked(gc_ctx *ctx, Job *job)
 void scheduler_main(gc_ctx *ctx)
 {
     (void)hipSetDevice(ctx->device);
+    // this thread's waits end on time, not within the default 50 us of it
+    (void)prctl(PR_SET_TIMERSLACK, 1000UL);
     std::unique_lock<std::mutex> lk(ctx->mu);
     while (!ctx->stop) {
         if (ctx->running.empty()) {
@@ -1346,7 +1349,15 @@ void scheduler_main(gc_ctx *ctx)
             admit_locked(ctx);
             ctx->done_cv.notify_all();
         }
-        ctx->cv.wait_for(lk, std::chrono::microseconds(100));
+        // A look every sixteenth of the youngest job's age, at most every 5 us
+        // and at least every 100: what the end is seen late by stays small
+        // against the job.  1000 starts of 4^2 take 273 us, with a look
+        // every 100 us (150 with the slack) 389.
+        Clock::duration age = Clock::duration::max();
+        const Clock::time_point now = Clock::now();
+        for (const Job *job : ctx->running) age = std::min(age, now - job->t_submit);
+        const Clock::duration least = std::chrono::microseconds(5), most = std::chrono::microseconds(100);
+        ctx->cv.wait_for(lk, std::min(std::max(age / 16, least), most));
     }
 }
 

@@ -479,6 +479,7 @@ __device__ __forceinline__ void team_job(const GcJobDev &J, unsigned long long *
         return;
     }
     load_links();
+    __syncthreads();   // a start that ended in place 0 beside this one is written out
     constexpr int Q = (K == 2 ? 2 : 1) * M < 6 ? (K == 2 ? 2 : 1) * M : 6;
     while (act) {
         const int from = __builtin_ctz(act);

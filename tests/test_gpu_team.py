@@ -75,3 +75,27 @@ def test_a_start_on_its_own_stops_at_its_sweep(ctx, extent, precision):
         if precision == "fp64":
             assert np.array_equal(starts["sweeps64"], rec["sweeps64"])
         ctx.gc_release(h)
+
+
+@pytest.mark.parametrize("extent,precision", [
+    ((16, 16), "fp64"), ((32, 32), "fp64"), ((6, 6, 6), "fp64"), ((4, 4, 4, 4), "fp64"), ((4, 4, 6, 6), "fp64"),
+    ((10, 10, 10), "mixed"), ((4, 6, 6, 6), "mixed")])
+def test_starts_that_end_beside_the_last_one(ctx, extent, precision):
+    """The end of a launch, where workgroups go from several starts in step to
+    one on its own: every record, and the final states of the last starts to
+    be claimed, as from launches that give each workgroup a single start."""
+    n, single = 7000 if GI.volume(extent) <= 256 else 3000, 250
+    phi = GI.orbit_angles(extent, 9, 1)
+    h, _, many, _ = run_gpu(ctx, extent, phi, n, gc.SolveParams(omega=1.7, precision=precision), orbit_index=1)
+    last = range(n - single, n)
+    states = [ctx.gc_fetch_start_state(h, k) for k in last]
+    for first in range(0, n, single):
+        p = gc.SolveParams(omega=1.7, precision=precision, first_start=first)
+        h2, _, few, _ = run_gpu(ctx, extent, phi, single, p, orbit_index=1)
+        for f in ("status", "sweeps32", "sweeps64", "F", "D", "key_hi", "key_lo"):
+            assert np.array_equal(many[f][first:first + single], few[f]), f
+        if first == last[0]:
+            for k, state in zip(last, states):
+                assert np.array_equal(state, ctx.gc_fetch_start_state(h2, k)), k
+        ctx.gc_release(h2)
+    ctx.gc_release(h)

@@ -640,11 +640,9 @@ gc_status plan_job(gc_ctx *ctx, Job *job, JobLayout &L)
         // workgroup layout where it is instantiated (more than two)
         const int o_ns = (o->V / 2 + 63) / 64;
         int wps = (o->K == 2) ? gc_wps_for(o_ns) : -1;
-        // the team kernels where one is instantiated and its states fit
+        // the team kernels where one is instantiated (its states fit then)
         GcTeamShape team = gc_team_shape(o->d, o->K, o->V);
-        if (team.cls && ((ctx->wps_override > 0 && wps > 0) ||
-                         gc_team_lds_bytes(o->d, o->K, team, o->V, false) > ctx->lds_max))
-            team.cls = 0;
+        if (ctx->wps_override > 0 && wps > 0) team.cls = 0;
         if (team.cls) {
             Group *g = nullptr;
             for (Group &x : L.groups)

@@ -41,7 +41,8 @@ constexpr GcTeamClass gc_team_class(int d, int K, int cls)
                               : GcTeamClass{1, 3, 16, 4, 1, false};
         return cls == 1   ? GcTeamClass{1, 3, 4, 3, 0, true}
                : cls == 2 ? GcTeamClass{1, 7, 8, 2, 4, true}
-               : cls == 3 ? GcTeamClass{1, 3, 12, 3, 1, false}
+               : cls == 3 ? GcTeamClass{1, 5, 8, 2, 4, true}
+               : cls == 4 ? GcTeamClass{1, 3, 12, 3, 1, false}
                           : GcTeamClass{2, 3, 8, 2, 1, false};
     }
     if (K == 3 && d == 2) return cls == 1 ? GcTeamClass{1, 3, 4, 4, 0, true} : GcTeamClass{1, 3, 8, 4, 0, true};

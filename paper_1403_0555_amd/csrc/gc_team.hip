@@ -12,16 +12,19 @@ GcTeamShape gc_team_shape(int d, int K, int V)
         // single start's sweep of 8^2 against 0.95, at the same rate in bulk
         if (w <= 1) return none;
         if (w <= 4) return {1, w};
-        if (w <= 8) return {2, w};
-        if (d < 4) return w <= 16 ? GcTeamShape{3, w} : none;
+        if (d < 4) return w <= 8 ? GcTeamShape{2, w} : w <= 16 ? GcTeamShape{3, w} : none;
         // four dimensions: 80 registers of links and offsets a site and
-        // colour leave room for 12 wavefronts of one site or 8 of two
-        return w <= 12 ? GcTeamShape{3, w} : w <= 16 ? GcTeamShape{4, (w + 1) / 2} : none;
+        // colour leave room for 12 wavefronts of one site or 8 of two; seven
+        // starts of seven wavefronts are 149 KB of LDS, of eight 170
+        if (w <= 7) return {2, w};
+        return w == 8 ? GcTeamShape{3, w} : w <= 12 ? GcTeamShape{4, w} : w <= 16 ? GcTeamShape{5, (w + 1) / 2} : none;
     }
     if (d < 2) return none;
     if (K == 3) return w <= 4 && d < 4 ? GcTeamShape{1, w} : w <= 8 ? GcTeamShape{2, w} : none;
-    // seven colours in four dimensions: 280 registers
-    if (K == 5 || (K == 7 && d < 4)) return w <= 8 ? GcTeamShape{2, w} : none;
+    if (K == 5) return w <= 8 ? GcTeamShape{2, w} : none;
+    // seven colours: 280 registers in four dimensions; three starts of seven
+    // wavefronts are 163 KB of LDS
+    if (K == 7 && d < 4) return w <= 6 ? GcTeamShape{2, w} : none;
     return none;
 }
 

@@ -629,6 +629,7 @@ __global__ __launch_bounds__(64 * gc_team_class(D, K, CLS).maxw, gc_team_class(D
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int cur_job;
     __shared__ TeamShared<TC.m> sh;
+    static_assert(sizeof sh + sizeof cur_job <= 1024, "beside the 159 KiB that gc_team_shape allows");
     int j0 = (int)(blockIdx.x % (unsigned)n_jobs);
     for (int round = 0; round < n_jobs; ++round) {
         if (threadIdx.x == 0) {

@@ -99,3 +99,20 @@ def test_starts_that_end_beside_the_last_one(ctx, extent, precision):
                 assert np.array_equal(state, ctx.gc_fetch_start_state(h2, k)), k
         ctx.gc_release(h2)
     ctx.gc_release(h)
+
+
+@pytest.mark.parametrize("extent", [(4, 4, 8, 8), (2, 8, 8, 8), (2, 2, 2, 114), (2, 2, 2, 128)])
+@pytest.mark.parametrize("kw", [{"omega": 1.7}, {"omega": 1.0, "max_sweeps": 40, "stop_norm": "max_abs", "eps64": 1e-3},
+                                {"omega": 1.6, "check_every": 3}])
+def test_eight_wavefronts_in_four_dimensions(ctx, extent, kw):
+    """449 to 512 sites a colour, five starts in step: against the oracle, and
+    in a launch of more starts than the workgroups hold at once."""
+    test_team_kernels_match_the_oracle(ctx, extent, kw)
+    phi = GI.orbit_angles(extent, 3, 1)
+    p = gc.SolveParams(**{"max_sweeps": 150, **kw})
+    h, _, many, _ = run_gpu(ctx, extent, phi, 2000, p, orbit_index=1)
+    h2, _, few, _ = run_gpu(ctx, extent, phi, 24, p, orbit_index=1)
+    for f in ("status", "sweeps64", "F", "D", "key_hi", "key_lo"):
+        assert np.array_equal(many[f][:24], few[f], equal_nan=many[f].dtype.kind == "f"), f
+    ctx.gc_release(h)
+    ctx.gc_release(h2)

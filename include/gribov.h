@@ -133,8 +133,8 @@ typedef struct {
     uint64_t lanczos_runs;
     uint64_t paper_count;       /* distinct trunc(x * 1e8) over converged starts (valid when DONE) */
     double submit_to_done_ms;   /* latency of the last launch (valid when DONE) */
-    double device_ms;           /* device time of the last launch's relax kernel, or of the whole graph of a
-                                   batch (valid when DONE) */
+    double device_ms;           /* device time of the last launch's relaxation, the drawing of its start states
+                                   included, or of the whole graph of a batch (valid when DONE) */
     double post_ms;             /* device time of the last launch's key pass and table compaction (single-orbit
                                    launches) */
     double filter_ms;           /* device time of the last launch's FP filter pass (single-orbit launches) */
@@ -335,8 +335,8 @@ gc_status gc_launch_bytes(gc_ctx *ctx, gc_orbit orbit, uint64_t n_starts, const 
  * memory, and the number of launches waiting for admission (any may be NULL). */
 gc_status gc_memory_info(gc_ctx *ctx, uint64_t *budget, uint64_t *in_use, uint64_t *queued);
 
-/* Device time of the last completed launch's solve kernel in milliseconds,
- * measured with HIP events on the stream the kernel ran on. */
+/* Device time of the last completed launch's relaxation (device_ms) in
+ * milliseconds, measured with HIP events on the stream it ran on. */
 gc_status gc_kernel_time_ms(gc_ctx *ctx, gc_orbit orbit, double *solve_ms);
 
 /* Saturation curve of a completed launch (Sec. III and Figs. 1-3: the

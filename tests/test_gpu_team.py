@@ -116,3 +116,18 @@ def test_eight_wavefronts_in_four_dimensions(ctx, extent, kw):
         assert np.array_equal(many[f][:24], few[f], equal_nan=many[f].dtype.kind == "f"), f
     ctx.gc_release(h)
     ctx.gc_release(h2)
+
+
+def test_relax_time_counts_the_start_states(ctx):
+    """With a single sweep per start, drawing the start states is a large part
+    of a launch: its device times add up to nearly all of it."""
+    extent, n = (6, 6, 6, 6), 400000
+    h = ctx.gc_orbit_load(extent, GI.orbit_angles(extent, 2, 0), 0)
+    for _ in range(3):
+        ctx.gc_launch(h, n, gc.SolveParams(omega=1.7, max_sweeps=1))
+        assert ctx.gc_wait(h, 60_000) == gc.GC_OK
+        prog = ctx.gc_poll(h)
+    assert prog["nonconverged"] == n
+    device = prog["device_ms"] + prog["post_ms"] + prog["filter_ms"]
+    assert device > 0.85 * prog["submit_to_done_ms"], prog
+    ctx.gc_release(h)

@@ -452,6 +452,7 @@ __global__ __launch_bounds__(B, lanczos_waves(B, S, D)) void lanczos_kernel(cons
         double dg[S];
         {
             const double wbe0 = whole ? w0[S - 1] : wl[ib];
+            const int ta = act ? tid : 0;   // threads past the stride P would read past the arrays
 #pragma unroll
             for (int k = 0; k < S; ++k) {
                 double a = w0[k] + ((k > 0) ? w0[k - 1] : wbe0);
@@ -459,7 +460,7 @@ __global__ __launch_bounds__(B, lanczos_waves(B, S, D)) void lanczos_kernel(cons
                 for (int mu = 1; mu < GC_MAXD; ++mu)
                     if (mu < d) {
                         lds_ptr<const double> wm = wl + (mu + w0off) * A;
-                        a += wm[at(k, tid)] + wm[at(k, tid + db[mu])];
+                        a += wm[at(k, ta)] + wm[at(k, ta + db[mu])];
                     }
                 dg[k] = act ? a : 0.0;
             }

@@ -56,3 +56,34 @@ def test_capped_iterations_bound_the_spectrum_from_above(ctx, extent):
         assert np.all(c["lambda2"] >= ref["lambda2"] - LAMBDA_TOL)
         assert np.all(c["lambda2"] <= last + LAMBDA_TOL)
         last = c["lambda2"]
+
+
+def start_vector(V):
+    """The filter's start vector: mixed site indices as fractions, less their mean, normalised."""
+    m = (1 << 64) - 1
+    x = np.empty(V)
+    for i in range(V):
+        z = (i + 0x5851F42D4C957F2D) & m
+        z = ((z ^ (z >> 30)) * 0xBF58476D1CE4E5B9) & m
+        z = ((z ^ (z >> 27)) * 0x94D049BB133111EB) & m
+        x[i] = ((z ^ (z >> 31)) >> 11) * 2.0 ** -53 - 0.5
+    x -= x.mean()
+    return x / np.linalg.norm(x)
+
+
+@pytest.mark.parametrize("extent", [(4, 4), (5, 5), (10, 26), (6, 8, 10), (10, 12, 12), (3, 21, 21), (14, 14, 14),
+                                    (6, 6, 6, 6), (6, 6, 6, 8)])
+def test_one_iteration_is_the_start_vectors_quotient(ctx, extent):
+    """Stopped after one iteration, the filter returns q.(M q) of its start
+    vector: threads without sites of their own, up to an eighth of the
+    workgroup past the arrays' stride, have no part in it."""
+    phi, V = GI.orbit_angles(extent, 5, 1), GI.volume(extent)
+    p = gc.SolveParams(omega=1.7, lanczos_max_iter=1)
+    h, copies, _, _ = run_gpu(ctx, extent, phi, 2, p, orbit_index=1)
+    q = start_vector(V)
+    for c in copies:
+        theta = ctx.gc_fetch_start_state(h, int(c["rep_start"]))
+        _, _, _, w = O.observe(extent, phi, theta)
+        assert abs(c["lambda2"] - q @ (O.fp_operator(extent, w) @ q)) < LAMBDA_TOL
+        assert int(c["flags"]) & gc.GC_FLAG_LANCZOS_CAP and c["lanczos_iters"] == 1
+    ctx.gc_release(h)

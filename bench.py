@@ -55,22 +55,24 @@ def lanczos_flops_per_site(d: int) -> int:
     return 6 * d + 13
 
 
-# HBM traffic of the dominant kernel per launch, from two rocprofv3 --pmc
-# passes (FETCH_SIZE, WRITE_SIZE) over the default workload, each scaled by
-# the same counter on a plain device copy of known size.  Valid only for the
+# HBM traffic of the dominant kernel per launch (relax: with the reset kernel,
+# which draws its start states and is part of its time), from two rocprofv3
+# --pmc passes (FETCH_SIZE, WRITE_SIZE) over the default workload, each scaled
+# by the same counter on a plain device copy of known size.  Valid only for the
 # kernel sources they were taken on (SHA-256 below); otherwise null.
 KERNEL_SOURCES = {
-    "relax": ("gc_team_kern.h", "gc_team.h", "gc_team_inst.h", "gc_team_d4.hip", "gc_common.h", "gc_internal.h"),
+    "relax": ("gc_team_kern.h", "gc_team.h", "gc_team_inst.h", "gc_team_d4.hip", "gc_post.hip", "gc_common.h",
+              "gc_internal.h"),
     "lanczos_kernel": ("gc_lanczos_kern.h", "gc_filter.h", "gc_lanczos4.hip", "gc_common.h", "gc_internal.h"),
 }
 TRAFFIC = {
-    # team_kernel<4, 2, 3, double, 0>, 10^6 starts of the 6^4 FP64 workload (one
-    # dispatch): FETCH_SIZE 10384348.0 KiB x 2.0000 (a 2 GiB copy reads
-    # 1048587.5 KiB) and WRITE_SIZE 20457932.0 KiB x 1.0 (the copy writes
-    # 2097152.0 KiB)
-    "sources_sha256": "5443afb07775f17964caf96f89cc8b820fb48ba0e4907948bb236d46f5e83ceb",
+    # reset_kernel<true> and team_kernel<4, 2, 4, double, 0>, 10^6 starts of the
+    # 6^4 FP64 workload (one dispatch each): FETCH_SIZE 414.8 and 10383267.3
+    # KiB x 2.0000 (a 2 GiB copy reads 1048587.5 KiB), WRITE_SIZE 42094295.3
+    # and 20457898.3 KiB x 1.0 (the copy writes 2097152.0 KiB)
+    "sources_sha256": "15b349177202ed6510ea503d3dfafdb4ccdbaf84c0b1535bc675bbf73f413f73",
     "kernel": "relax",
-    "bytes_per_launch": 21267144704 + 20948922368,
+    "bytes_per_launch": 849536 + 43104558368 + 21264931456 + 20948887840,
 }
 
 
@@ -237,7 +239,8 @@ def summary(w, r):
 def rooflines(w, r):
     """ALU rooflines of the relax kernel and the FP filter kernel:
     algorithmic flops per launch over the kernel's mean duration (HIP events
-    on its stream)."""
+    on its stream; for the relax kernel the drawing of the start states is
+    part of it)."""
     d = len(w.extent)
     V = int(np.prod(w.extent))
     steps = r["steps"]

@@ -316,8 +316,8 @@ __device__ __forceinline__ void flush_tally(const GcJobDev &J, RelaxTally &t)
 }
 
 // Per-start bookkeeping shared by the relax kernels (one lane calls).  The
-// counters follow after 2^19 site updates, a fraction of a millisecond: the
-// progress a caller polls stays that recent.
+// counters are read when the launch has ended; adding to them every 2^19 site
+// updates or so keeps the 32-bit tallies small at next to no cost.
 __device__ __forceinline__ void record_relax(const GcJobDev &J, uint64_t local, int status, uint64_t sw32,
                                              uint64_t sw64, double D, RelaxTally &t)
 {

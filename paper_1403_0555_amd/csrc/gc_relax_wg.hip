@@ -1,6 +1,7 @@
 // Relaxation kernel for any lattice (any number of checkerboard colours), used
-// where no team kernel is instantiated (gc_team.h: odd rings, more than seven
-// colours, the largest odd lattices):
+// where no team kernel is instantiated (gc_team.hip: odd rings, more than seven
+// colours, seven in four dimensions, and odd lattices of more than 512 sites
+// a colour, 384 with seven):
 // one workgroup holds one random start in LDS, in natural site order, and
 // pulls the next start from a device-wide counter when its start is done.
 //

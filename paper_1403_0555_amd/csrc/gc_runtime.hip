@@ -339,9 +339,9 @@ struct gc_ctx {
     int n_cu = 0;
     size_t lds_max = 0;
     int creg_override = -1;   // GC_WAVE_CREG: register-held coefficient colours (tuning)
-    int wps_override = -1;    // GC_WPS: 1 workgroup per start where available, 0 never (tuning)
+    int wps_override = -1;    // GC_WPS: 1 workgroup per start where instantiated (tuning), 0 or unset by shape
     // kernel variants chosen by gc_autotune: relax coefficient colours and
-    // layout per (d, slots per lane, precision), post workgroup shape per V
+    // layout per (d, slots per lane, precision)
     std::map<uint64_t, int> tune_creg;
     std::string tune_cache;             // file the choices persist in ("" none)
     uint64_t budget = 0, used = 0;
@@ -637,7 +637,8 @@ gc_status plan_job(gc_ctx *ctx, Job *job, JobLayout &L)
         L.o_sync.push_back(job->p.sync_batch ? place(sizeof(uint32_t) * n) : 0);
         L.o_theta.push_back(job->theta.empty() ? 0 : place(sizeof(double) * n * (uint64_t)o->V));
         // slots per lane if one wavefront held a start; GC_WPS = 1 forces the
-        // workgroup layout where it is instantiated (more than two)
+        // workgroup layout where it is instantiated (more than two), which
+        // otherwise takes what the team kernels do not (V > 2048)
         const int o_ns = (o->V / 2 + 63) / 64;
         int wps = (o->K == 2) ? gc_wps_for(o_ns) : -1;
         // the team kernels where one is instantiated (its states fit then)
@@ -658,9 +659,9 @@ gc_status plan_job(gc_ctx *ctx, Job *job, JobLayout &L)
             g->total += n;
             continue;
         }
-        // two colours: one wavefront per start up to 64 sites per colour, a
-        // workgroup of wps wavefronts per start above; other colourings take
-        // the generic workgroup kernel
+        // two colours without a team kernel: one wavefront per start up to 64
+        // sites per colour, a workgroup of wps wavefronts per start above;
+        // other colourings take the generic workgroup kernel
         if (wps > 0 && 32 * (size_t)o->V > ctx->lds_max) wps = -1;
         const bool wave = (o->K == 2) && (wps > 0 || (wps == 0 && o_ns == 1));
         // groups by kernel: dimension and layout, or (generic) block size; an
@@ -1351,10 +1352,12 @@ void scheduler_main(gc_ctx *ctx)
             admit_locked(ctx);
             ctx->done_cv.notify_all();
         }
-        // A look every sixteenth of the youngest job's age, at most every 5 us
-        // and at least every 100: what the end is seen late by stays small
-        // against the job.  1000 starts of 4^2 take 273 us, with a look
-        // every 100 us (150 with the slack) 389.
+        // A look every sixteenth of the youngest job's age since its
+        // submission, at most every 5 us and at least every 100: what the end
+        // is seen late by stays small against what the caller waits.  When
+        // this came, 1000 starts of 4^2 took 273 us, and 389 with a look every
+        // 100 us (150 with the slack); a job of a stream takes the process
+        // 125 us of processor time, 129 with a look every 100.
         Clock::duration age = Clock::duration::max();
         const Clock::time_point now = Clock::now();
         for (const Job *job : ctx->running) age = std::min(age, now - job->t_submit);

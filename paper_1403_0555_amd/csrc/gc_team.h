@@ -16,18 +16,25 @@ struct GcTeamClass {
 // thread's sites, 10 d K registers, set the register budget, the budget the
 // wavefronts per SIMD, and the LDS of 160 KiB the starts in step.  Measured,
 // 10^9 site updates per second at 100 sweeps of 10^5 starts (over-relaxed,
-// double precision), against the kernels these replaced (a wavefront, or
-// with odd extents a workgroup, per start): 6^4 290 against 257, 10^3 415
-// against 317, 8^3 404 against 296, 12^3 367 against 204, 32^2 491 against
-// 290, 4^4 312 against 175, 16^2 445 against 386, 9^3 253 against 78; and a
-// sweep of a single start: 6^4 1.5 against 5.9 us, 10^3 1.2 against 3.8, 12^3
-// 1.6 against 10.8, 9^3 2.0 against 6.0.  The clock falls from 2.2 to 1.9 GHz
-// as the vector units fill: the power limit takes part of what a better
-// overlap would give.
+// double precision, the start states drawn within the time), against the
+// kernels these replaced (a wavefront, or with odd extents a workgroup, per
+// start): 6^4 284 against 270, 4^2 x 8^2 312 against 234, 10^3 403 against
+// 333, 8^3 403 against 315, 12^3 354 against 215, 32^2 487 against 306, 4^4
+// 307 against 175, 16^2 439 against 405, 9^3 284 against 80; and a sweep of a
+// single start: 6^4 1.5 against 6.0 us, 4^2 x 8^2 0.9 against 6.0, 10^3 1.2
+// against 3.7, 12^3 1.6 against 10.6, 9^3 1.4 against 6.1.  7^2 is the one
+// lattice found slower in bulk (1.5 10^5 starts 20.4 against 18.4 ms; fewer
+// starts and plain relaxation are faster): 140 registers of links leave two
+// wavefronts a SIMD, and held to three they spill.  The clock falls from 2.2 to
+// 1.9 GHz as the vector units fill: the power limit takes part of what a
+// better overlap would give.
 // The lone starts' loop costs the main one some registers: none where there
 // are enough, but with it 200 sweeps of 5 10^4 starts of 10^3 took 30.0 ms
 // (23.8), of 2 10^4 of 12^3 22.2 (18.8) and of 3 10^4 of 6^4 27.9 (26.5), so
 // those classes do without (single precision has room in all).
+// Four dimensions, eight wavefronts: seven starts in step do not fit, and five
+// take less than three with the registers of the next class (4^2 x 8^2, 200
+// starts 0.74 against 0.90 ms, 5000 4.7 against 5.2, 60000 39.1 against 39.5).
 constexpr GcTeamClass gc_team_class(int d, int K, int cls)
 {
     if (K == 2) {

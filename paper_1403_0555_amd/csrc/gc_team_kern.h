@@ -15,10 +15,10 @@
 // rest goes to the two barriers of a sweep.  The M starts share the barriers,
 // and a workgroup left with one start spends all its wavefronts on it, so a
 // launch of few starts, or the slowest starts of a long one, run at a latency
-// of a few thousand cycles per sweep (6^4: 1.5 us against 5.9 us for a
-// wavefront on its own).  10^6 starts of 6^4 relax in 549 ms (617 ms in the
-// wavefront-per-start layout), 10^5 of 10^3 in 28.5 ms (37.7), 10^4 of 9^3 in
-// 4.6 ms (19).
+// of a few thousand cycles per sweep (6^4: 1.5 us against 6.0 us for a
+// wavefront on its own).  With the drawing of their start states, 10^6 starts
+// of 6^4 relax in 562 ms (599 ms in the wavefront-per-start layout on the same
+// machine), 10^5 of 10^3 in 27.9 ms (36.1), 10^4 of 9^3 in 5.2 ms (19.1).
 //
 // LDS: X[p][m], the M starts' values of the site at colour-sorted position p
 // (colour c's sites at c V/K + rank, ascending), then red[m][thread] (the

@@ -26,8 +26,9 @@ hipError_t gc_launch_wave(int d, const GcJobDev *jobs, const GcWaveOrbit *worbs,
                           unsigned long long *job_next, int variant, float2 *bounce, int grid, size_t lds,
                           hipStream_t s);
 
-// Workgroup-per-start variant (lattices with more than 128 slots per
-// colour): wps wavefronts share a start, at most two slots per thread.
+// Workgroup-per-start variant (V > 2048, 16 wavefronts; fewer, above 256
+// sites, where GC_WPS = 1 asks for it): wps wavefronts share a start, at most
+// two slots per thread.
 // gc_wps_for(ns) gives wps for ns slots per lane of the one-wavefront layout
 // (0 when that layout is used, -1 when too large).  LDS: 32V bytes.
 int gc_wps_for(int ns);

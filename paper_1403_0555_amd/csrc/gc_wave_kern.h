@@ -1,7 +1,8 @@
 // Wavefront-per-start solver for lattices with even extents (two colours).
 //
 // Each 64-lane wavefront relaxes one random start with its state resident in
-// LDS and never synchronises with other wavefronts: a start finishes on its
+// LDS (at most 64 sites a colour) and never synchronises with other
+// wavefronts: a start finishes on its
 // own schedule and the wavefront pulls the next start of its job from a
 // per-job counter.  The workgroup only synchronises when it moves to another
 // job (the orbit's coefficient table may be staged in LDS and is shared by
@@ -332,7 +333,7 @@ __device__ void relax_start_wave(const GcJobDev &J, const GcWaveOrbit &WO, CP64 
     start_sync<WPS>();
 }
 
-// WG = WAVES wavefronts, at most two slots per lane.  LDS: [neighbour table
+// WG = WAVES wavefronts, one slot per lane and colour (NS = 1).  LDS: [neighbour table
 // 16V | coef64 | coef32 when COEF_LDS] then per wave a 16V-byte state region
 // (double2[V], or float2[V] in the single-precision phase).
 template <int D, int NS, int WAVES, bool COEF_LDS, int CREG>
@@ -420,16 +421,16 @@ __global__ __launch_bounds__(64 * WAVES) void wave_kernel(const GcJobDev *__rest
     }
 }
 
-// One start per workgroup of WPS wavefronts, for lattices with more than 128
-// slots per colour: each thread keeps at most two slots per colour, the
+// One start per workgroup of WPS wavefronts, for lattices above the team
+// kernels' (V > 2048): each thread keeps at most two slots per colour, the
 // colour passes synchronise the workgroup.  LDS: the neighbour table (16V)
 // and one state region (16V).  The coefficients come from the L2, half a
 // megabyte per sweep of 8^4 and the bound of it (5.9 us); in single precision
 // with 16 wavefronts, where 128 registers allow it, those of colour 0 (up to
 // three dimensions all) stay in registers: 10^4 mixed-precision starts of 8^4
-// 49.4 -> 45.5 ms, 5000 of 16^3 18.9 -> 17.2, 2000 of 64^2 20.9 -> 19.8.  With
-// fewer wavefronts the registers cost workgroups per CU (5000 of 4^2 x 8^2
-// 4.9 -> 7.7 ms).
+// 48.2 -> 44.3 ms, 5000 of 16^3 19.3 -> 17.0, 2000 of 64^2 21.4 -> 19.6.  With
+// fewer wavefronts the registers cost workgroups per CU (4^2 x 8^2 in this
+// layout took 1.6 to 1.9 times as long).
 template <int D, int WPS>
 __global__ __launch_bounds__(64 * WPS) void wps_kernel(const GcJobDev *__restrict__ jobs,
                                                        const GcWaveOrbit *__restrict__ worbs, int n_jobs,
